@@ -225,8 +225,7 @@ int post_split_parts(long long R, int D, int F);
 size_t post_part_bytes(long long R, int D, int F);
 hipError_t launch_gemm(const GemmArgs& a, bool bf16_model, hipStream_t s);   // fp32 models
 hipError_t launch_proj(const GemmArgs& a, hipStream_t s);                    // bf16 models, K = d
-// bf16 models with d >= 256: 128 x 128 tiles, LDS-staged operands; A bf16 without LayerNorm
-// (ln_g == nullptr), K a multiple of 64, N of 128.
+// Wide bf16 models (d = 512): A bf16 without LayerNorm (ln_g == nullptr), K and N multiples of 128.
 bool gemm_tiled_fits(int K, int N);
 hipError_t launch_gemm_tiled(const GemmArgs& a, hipStream_t s);
 hipError_t launch_attention(const AttnArgs& a, bool bf16_model, hipStream_t s);
