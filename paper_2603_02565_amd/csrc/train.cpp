@@ -280,10 +280,11 @@ hipError_t linear_dw(const float* X, long long x_rs, int R, int din, const float
   g.C = dW; g.c_rs = dout;
   g.M = din; g.N = dout; g.K = R;
   g.beta = 1.f;
-  // enough (row chunk x output tile) workgroups to fill the chip; chunks of at least 256 rows
+  // (row chunk x output tile) workgroups: one round of the chip's four per compute unit, in chunks of at
+  // least 64 rows (two k steps)
   const long long tiles = (long long)((din + 63) / 64) * ((dout + 63) / 64);
-  long long chunks = std::max(1LL, 2048 / tiles);
-  long long ks = std::max(256LL, (R + chunks - 1) / chunks);
+  long long chunks = std::max(1LL, 1024 / tiles);
+  long long ks = std::max(64LL, (R + chunks - 1) / chunks);
   g.ksplit = (int)((ks + 31) / 32 * 32);
   g.colsum = db;
   return t_gemm(g, s);

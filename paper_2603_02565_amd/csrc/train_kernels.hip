@@ -18,172 +18,215 @@ namespace {
 // fp32 matrix cores: a workgroup of four waves owns a (32 WM) x (32 WN) output tile, each wave one
 // 32 x 32 block accumulated by v_mfma_f32_32x32x2_f32 (lane l feeds A[l%32][l/32] and
 // B[l/32][l%32] of a 32x32x2 step and holds D[8q + 4(l/32) + e][l%32] in accumulator 4q + e).
-// k advances in steps of 32 through LDS, the next step's operands loaded into registers while
-// the current step's products run.  AK / BK: the operand's k index is its contiguous one,
-// so consecutive lanes load along k (else along i or j), which keeps the global loads coalesced
-// for both orientations.
+// k advances in steps of 32 through LDS.  AK / BK: the operand's k index is its contiguous one, so
+// consecutive lanes load along k (else along i or j), which keeps the global loads coalesced for
+// both orientations.
 // ------------------------------------------------------------------------------------------
 constexpr int GK = 32;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// One operand's tile of T rows (i or j) by GK k values, through registers into LDS.
+//   KC:  k contiguous in memory -> LDS [row][k], rows of GK + 4 floats (a wave half's 16-byte reads of
+//        32 rows fall on every bank group once);
+//   !KC: rows contiguous        -> LDS [k][row], rows of T + 8 floats (the two wave halves read k
+//        and k + 4, which lie 32 banks apart).
+// Either way the store keeps the orientation of the load, 16 bytes at a time (VEC).
+// MFMA c of the group of eight k values from 8s takes k = 8s + 4 (l/32) + c, for both operands.
+template <int T, bool KC, bool VEC>
+struct TOperand {
+  static constexpr int N = GK * T / 256;                    // values per thread and step
+  static constexpr int LD = KC ? GK + 4 : T + 8, SIZE = KC ? T * LD : GK * LD;
+  static constexpr int W = VEC ? 4 : 1, NG = N / W;         // values per load, loads
+  static constexpr unsigned OUT = 0x80000000u;              // past every buffer below: such a load gives zeros
+  const float* base;                                        // row 0 of the tile at k = 0 (uniform)
+  unsigned off[NG];                                         // this thread's byte offsets at a step's first k
+  long long ks;                                             // stride of k
+  float r[N];
+  // rows of the tile at row0 .. rows - 1; base0 is the matrix.  Rows past the last get OUT.
+  FE_DEV void init(const float* base0, int row0, int rows, long long rs, long long ks_) {
+    base = base0 + row0 * rs;
+    ks = ks_;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int e = threadIdx.x + 256 * q;
+      const int row = KC ? e / (GK / W) : W * (e % (T / W)), kk = KC ? W * (e % (GK / W)) : e / (T / W);
+      off[q] = row0 + row < rows ? 4u * (unsigned)(row * (int)rs + kk * (int)ks_) : OUT;
+    }
+  }
+  // the values of step k0, k < kend (a group of W lies inside or outside as a whole: the launcher
+  // checks that the contiguous extent is a multiple of W).  Loads only: no branch between them, so
+  // all of a step's are in flight together.
+  FE_DEV void load(int k0, int kend) {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + k0 * ks), 0, 0x7ffffffc, 0x00027000);
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int e = threadIdx.x + 256 * q;
+      const int kk = KC ? W * (e % (GK / W)) : e / (T / W);
+      const unsigned o = k0 + kk < kend ? off[q] : OUT;
+      if constexpr (VEC) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) r[4 * q + c] = __uint_as_float(v[c]);
+      } else {
+        r[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, o, 0, 0));
+      }
+    }
+  }
+  FE_DEV void store(float* S) const {
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int e = threadIdx.x + 256 * q;
+      float* d = S + (KC ? (e / (GK / W)) * LD + W * (e % (GK / W)) : (e / (T / W)) * LD + W * (e % (T / W)));
+      if constexpr (VEC) *reinterpret_cast<float4*>(d) = make_float4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
+      else *d = r[q];
+    }
+  }
+  // the lane's operands of the four MFMAs of k group s, for the 32 rows from w
+  static FE_DEV void frag(const float* S, int w, int s, float (&v)[4]) {
+    const int lr = threadIdx.x & 31, lk = (threadIdx.x >> 5) & 1;
+    if constexpr (KC) {
+      const float4 t = *reinterpret_cast<const float4*>(&S[(w + lr) * LD + 8 * s + 4 * lk]);
+      v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = S[(8 * s + 4 * lk + c) * LD + w + lr];
+    }
+  }
+};
+
+// What bounds it: at K = d = 128 a tile has four k steps, so the latencies around them count as much
+// as the products.  Hence: operands by buffer loads whose bounds the hardware checks (no branch
+// between them, so a step's loads share one latency), LDS in two buffers (the next step's loads run
+// behind this step's products, one barrier per step), the epilogue's residual / mask / old-C
+// values all requested before the first store (C may alias them as far as the compiler knows, so
+// loads written between the stores are waited for one by one), and the tiles numbered so that one
+// XCD's L2 serves the column tiles of a row tile.  Measured, before and after: a 385 x 64 x 64
+// product 9.3 -> 4.2 us; 16384 x 384 x 128 25.8 -> 23.2 us (67 TFLOP/s; its output alone is 25 MB);
+// a training step of 385 context rows (d 64) 1984 -> 1390 us, of 16384 (d 128) 5632 -> 4962 us.
 template <int WM, int WN, bool AK, bool BK, bool VA, bool VB>
-__global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz) {
+__global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles_n, int tiles) {
   static_assert(WM * WN == 4, "four waves");
-  constexpr int TM = 32 * WM, TN = 32 * WN, PA = TM + 4, PB = TN + 4;
-  constexpr int NA = GK * TM / 256, NB = GK * TN / 256;   // elements per thread per k-step
-  __shared__ __align__(16) float As[GK][PA];
-  __shared__ __align__(16) float Bs[GK][PB];
-  const int zz = z0 + blockIdx.z, z = zz % nz, kc = zz / nz;
+  constexpr int TM = 32 * WM, TN = 32 * WN;
+  using OA = TOperand<TM, AK, VA>;
+  using OB = TOperand<TN, BK, VB>;
+  __shared__ __align__(16) float As[2][OA::SIZE];
+  __shared__ __align__(16) float Bs[2][OB::SIZE];
+  const int id = xcd_tile(blockIdx.x, gridDim.x);   // tiles of one batch item (or k chunk) are neighbours
+  const int zz = z0 + id / tiles, tile = id % tiles;
+  const int z = zz % nz, kc = zz / nz;
   const int z1 = z / g.nb2, z2 = z % g.nb2;
   const int kbeg = g.ksplit > 0 ? kc * g.ksplit : 0;
   const int kend = g.ksplit > 0 ? min(g.K, kbeg + g.ksplit) : g.K;
-  const float* A = g.A + z1 * g.a_b1 + z2 * g.a_b2;
-  const float* B = g.B + z1 * g.b_b1 + z2 * g.b_b2;
-  float* C = g.C + z1 * g.c_b1 + z2 * g.c_b2;
-  const float* Rz = g.R + z1 * g.c_b1 + z2 * g.c_b2;
-  const float* Mz = g.mask + z1 * g.c_b1 + z2 * g.c_b2;
-  const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int ti = tile / tiles_n, tj = tile % tiles_n;
+  const int i0 = ti * TM, j0 = tj * TN;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wi = (wave / WN) * 32, wj = (wave % WN) * 32;
   const int lr = lane & 31, lk = lane >> 5;
-  float ra[NA], rb[NB];
-  // the operands of k-step k0 into registers (zero outside the matrices and past kend).  VA / VB:
-  // four consecutive elements of the contiguous index per load (the launcher has checked that
-  // they are 16-byte aligned); NA / NB stay the number of scalars per thread.
+  OA a;
+  OB b;
+  a.init(g.A + z1 * g.a_b1 + z2 * g.a_b2, i0, g.M, g.a_rs, g.a_cs);
+  b.init(g.B + z1 * g.b_b1 + z2 * g.b_b2, j0, g.N, g.b_cs, g.b_rs);
   auto load = [&](int k0) {
-    if constexpr (VA) {
-#pragma unroll
-      for (int q = 0; q < NA / 4; ++q) {
-        const int e = threadIdx.x + 256 * q;
-        const int i = AK ? i0 + e / (GK / 4) : i0 + 4 * (e % (TM / 4));
-        const int k = AK ? k0 + 4 * (e % (GK / 4)) : k0 + e / (TM / 4);
-        const float* src = A + i * g.a_rs + k * g.a_cs;
-        if (AK ? (i < g.M && k + 3 < kend) : (i + 3 < g.M && k < kend)) {
-          const float4 v = *reinterpret_cast<const float4*>(src);
-          ra[4 * q] = v.x; ra[4 * q + 1] = v.y; ra[4 * q + 2] = v.z; ra[4 * q + 3] = v.w;
-        } else {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            ra[4 * q + c] = (AK ? (i < g.M && k + c < kend) : (i + c < g.M && k < kend))
-                                ? src[AK ? c : c * g.a_rs] : 0.f;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < NA; ++t) {
-        const int e = threadIdx.x + 256 * t;
-        const int kk = AK ? e % GK : e / TM, mm = AK ? e / GK : e % TM;
-        const int i = i0 + mm, k = k0 + kk;
-        ra[t] = (i < g.M && k < kend) ? A[i * g.a_rs + k * g.a_cs] : 0.f;
-      }
-    }
-    if constexpr (VB) {
-#pragma unroll
-      for (int q = 0; q < NB / 4; ++q) {
-        const int e = threadIdx.x + 256 * q;
-        const int j = BK ? j0 + e / (GK / 4) : j0 + 4 * (e % (TN / 4));
-        const int k = BK ? k0 + 4 * (e % (GK / 4)) : k0 + e / (TN / 4);
-        const float* src = B + k * g.b_rs + j * g.b_cs;
-        if (BK ? (j < g.N && k + 3 < kend) : (j + 3 < g.N && k < kend)) {
-          const float4 v = *reinterpret_cast<const float4*>(src);
-          rb[4 * q] = v.x; rb[4 * q + 1] = v.y; rb[4 * q + 2] = v.z; rb[4 * q + 3] = v.w;
-        } else {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            rb[4 * q + c] = (BK ? (j < g.N && k + c < kend) : (j + c < g.N && k < kend))
-                                ? src[BK ? c : c * g.b_cs] : 0.f;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < NB; ++t) {
-        const int e = threadIdx.x + 256 * t;
-        const int kk = BK ? e % GK : e / TN, nn = BK ? e / GK : e % TN;
-        const int j = j0 + nn, k = k0 + kk;
-        rb[t] = (j < g.N && k < kend) ? B[k * g.b_rs + j * g.b_cs] : 0.f;
-      }
-    }
-  };
-  auto store = [&]() {
-    if constexpr (VA) {
-#pragma unroll
-      for (int q = 0; q < NA / 4; ++q) {
-        const int e = threadIdx.x + 256 * q;
-        if constexpr (AK) {
-          const int mm = e / (GK / 4), kq = 4 * (e % (GK / 4));
-#pragma unroll
-          for (int c = 0; c < 4; ++c) As[kq + c][mm] = ra[4 * q + c];
-        } else {
-          *reinterpret_cast<float4*>(&As[e / (TM / 4)][4 * (e % (TM / 4))]) =
-              make_float4(ra[4 * q], ra[4 * q + 1], ra[4 * q + 2], ra[4 * q + 3]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < NA; ++t) {
-        const int e = threadIdx.x + 256 * t;
-        As[AK ? e % GK : e / TM][AK ? e / GK : e % TM] = ra[t];
-      }
-    }
-    if constexpr (VB) {
-#pragma unroll
-      for (int q = 0; q < NB / 4; ++q) {
-        const int e = threadIdx.x + 256 * q;
-        if constexpr (BK) {
-          const int nn = e / (GK / 4), kq = 4 * (e % (GK / 4));
-#pragma unroll
-          for (int c = 0; c < 4; ++c) Bs[kq + c][nn] = rb[4 * q + c];
-        } else {
-          *reinterpret_cast<float4*>(&Bs[e / (TN / 4)][4 * (e % (TN / 4))]) =
-              make_float4(rb[4 * q], rb[4 * q + 1], rb[4 * q + 2], rb[4 * q + 3]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < NB; ++t) {
-        const int e = threadIdx.x + 256 * t;
-        Bs[BK ? e % GK : e / TN][BK ? e / GK : e % TN] = rb[t];
-      }
-    }
+    a.load(k0, kend);
+    b.load(k0, kend);
   };
   f32x16 acc = {};
-  const bool csum = g.colsum && blockIdx.y == 0 && threadIdx.x < TN;   // first row tile: column sums of B
+  // first row tile: column sums of B, 256 / TN threads per column
+  const bool csum = g.colsum && ti == 0;
   float cs = 0.f;
   load(kbeg);
-  for (int k0 = kbeg; k0 < kend; k0 += GK) {
-    store();
-    __syncthreads();
-    if (k0 + GK < kend) load(k0 + GK);   // the next step's loads are in flight during this step's products
+  a.store(As[0]);
+  b.store(Bs[0]);
+  lds_barrier();
+  int cur = 0;
+  for (int k0 = kbeg; k0 < kend; k0 += GK, cur ^= 1) {
+    const bool more = k0 + GK < kend;
+    if (more) load(k0 + GK);
+    const float *Ac = As[cur], *Bc = Bs[cur];
+    float av[2][4], bv[2][4];                       // group s + 1 is read behind the products of group s
+    OA::frag(Ac, wi, 0, av[0]);
+    OB::frag(Bc, wj, 0, bv[0]);
 #pragma unroll
-    for (int t = 0; t < GK / 2; ++t)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[2 * t + lk][wi + lr], Bs[2 * t + lk][wj + lr], acc, 0, 0, 0);
-    if (csum)
+    for (int s = 0; s < GK / 8; ++s) {
+      if (s + 1 < GK / 8) {
+        OA::frag(Ac, wi, s + 1, av[(s + 1) & 1]);
+        OB::frag(Bc, wj, s + 1, bv[(s + 1) & 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int kk = 0; kk < GK; ++kk) cs += Bs[kk][threadIdx.x];
-    __syncthreads();
+      for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s & 1][c], bv[s & 1][c], acc, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (csum) {
+      const int jj = threadIdx.x % TN, part = threadIdx.x / TN;
+      constexpr int KP = GK * TN / 256;
+#pragma unroll
+      for (int t = 0; t < KP; ++t) cs += BK ? Bc[jj * OB::LD + part * KP + t] : Bc[(part * KP + t) * OB::LD + jj];
+    }
+    if (more) {
+      a.store(As[cur ^ 1]);   // last read one step ago, before the barrier that ended it
+      b.store(Bs[cur ^ 1]);
+    }
+    lds_barrier();
   }
-  if (csum && j0 + (int)threadIdx.x < g.N) atomicAdd(&g.colsum[j0 + threadIdx.x], g.alpha * cs);
+  if (csum) {
+    As[0][threadIdx.x] = cs;
+    lds_barrier();
+    if (threadIdx.x < TN && j0 + (int)threadIdx.x < g.N) {
+      float t = 0.f;
+#pragma unroll
+      for (int p = 0; p < 256 / TN; ++p) t += As[0][p * TN + threadIdx.x];
+      atomicAdd(&g.colsum[j0 + threadIdx.x], g.alpha * t);
+    }
+  }
   const int j = j0 + wj + lr;
   if (j >= g.N) return;
+  const int ib = i0 + wi + 4 * lk;                  // row of accumulator 4q + e: ib + 8q + e
+  const long long zo = z1 * g.c_b1 + z2 * g.c_b2 + j;
+  float* C = g.C + zo;
+  if (g.ksplit > 0) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = i0 + wi + 8 * q + 4 * lk + e;
-      if (i >= g.M) continue;
-      float r = g.alpha * acc[4 * q + e];
-      const long long o = i * g.c_rs + j;
-      float* c = C + o;
-      if (g.ksplit > 0) {
-        atomicAdd(c, r);
-        continue;
-      }
-      if (g.bias) r += g.bias[j];
-      if (g.R) r += Rz[o];
-      if (g.relu) r = fmaxf(r, 0.f);
-      if (g.mask && !(Mz[o] > 0.f)) r = 0.f;
-      *c = g.beta != 0.f ? r + g.beta * *c : r;
+    for (int t = 0; t < 16; ++t) {
+      const int i = ib + 8 * (t >> 2) + (t & 3);
+      if (i < g.M) atomicAdd(C + i * g.c_rs, g.alpha * acc[t]);
     }
+    return;
+  }
+  // rows past M read row M - 1, so every load is unconditional
+  auto at = [&](int t) { return min(ib + 8 * (t >> 2) + (t & 3), g.M - 1) * g.c_rs; };
+  float r[16];
+  const float bias = g.bias ? g.bias[j] : 0.f;
+#pragma unroll
+  for (int t = 0; t < 16; ++t) r[t] = g.alpha * acc[t] + bias;
+  if (g.R) {
+    float v[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) v[t] = g.R[zo + at(t)];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) r[t] += v[t];
+  }
+  if (g.relu)
+#pragma unroll
+    for (int t = 0; t < 16; ++t) r[t] = fmaxf(r[t], 0.f);
+  if (g.mask) {
+    float v[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) v[t] = g.mask[zo + at(t)];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) r[t] = v[t] > 0.f ? r[t] : 0.f;
+  }
+  if (g.beta != 0.f) {
+    float v[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) v[t] = C[at(t)];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) r[t] += g.beta * v[t];
+  }
+#pragma unroll
+  for (int t = 0; t < 16; ++t) {
+    const int i = ib + 8 * (t >> 2) + (t & 3);
+    if (i < g.M) C[i * g.c_rs] = r[t];
+  }
 }
 
 // Batched products with M, N <= 32 (attention inside short sequences): each wave owns one batch
@@ -695,24 +738,24 @@ inline unsigned blocks(long long n) { return (unsigned)((n + 255) / 256); }
 template <int WM, int WN, bool AK, bool BK, bool VA, bool VB>
 void gemm_launch(const TGemm& g, long long total, hipStream_t s) {
   constexpr int TM = 32 * WM, TN = 32 * WN;
-  const dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), 1);
-  for (long long z0 = 0; z0 < total; z0 += 65535) {
-    dim3 gz = grid;
-    gz.z = (unsigned)std::min<long long>(65535, total - z0);
-    hipLaunchKernelGGL((k_gemm<WM, WN, AK, BK, VA, VB>), gz, dim3(256), 0, s, g, (int)z0, g.nbatch);
-  }
+  const int tiles_n = (g.N + TN - 1) / TN, tiles = tiles_n * ((g.M + TM - 1) / TM);
+  const long long per = std::max(1LL, (1LL << 22) / tiles);   // batch items or k chunks per launch
+  for (long long z0 = 0; z0 < total; z0 += per)
+    hipLaunchKernelGGL((k_gemm<WM, WN, AK, BK, VA, VB>), dim3((unsigned)(std::min(per, total - z0) * tiles)), dim3(256), 0, s, g,
+                       (int)z0, g.nbatch, tiles_n, tiles);
 }
 
 // float4 loads of an operand are possible when its base and every stride but the contiguous one
-// are multiples of four floats (so every group of four along the contiguous index is aligned)
-inline bool vec4(const float* p, long long other_stride, long long b1, long long b2) {
-  return reinterpret_cast<uintptr_t>(p) % 16 == 0 && other_stride % 4 == 0 && b1 % 4 == 0 && b2 % 4 == 0;
+// are multiples of four floats (so every group of four along the contiguous index is aligned) and so
+// is the extent of the contiguous index (so no group is cut)
+inline bool vec4(const float* p, long long other_stride, long long b1, long long b2, int extent) {
+  return reinterpret_cast<uintptr_t>(p) % 16 == 0 && other_stride % 4 == 0 && b1 % 4 == 0 && b2 % 4 == 0 && extent % 4 == 0;
 }
 
 template <int WM, int WN, bool AK, bool BK>
 void gemm_vec(const TGemm& g, long long total, hipStream_t s) {
-  const bool va = vec4(g.A, AK ? g.a_rs : g.a_cs, g.a_b1, g.a_b2) && (AK ? g.a_cs == 1 : g.a_rs == 1);
-  const bool vb = vec4(g.B, BK ? g.b_cs : g.b_rs, g.b_b1, g.b_b2) && (BK ? g.b_rs == 1 : g.b_cs == 1);
+  const bool va = vec4(g.A, AK ? g.a_rs : g.a_cs, g.a_b1, g.a_b2, AK ? g.K : g.M) && (AK ? g.a_cs == 1 : g.a_rs == 1);
+  const bool vb = vec4(g.B, BK ? g.b_cs : g.b_rs, g.b_b1, g.b_b2, BK ? g.K : g.N) && (BK ? g.b_rs == 1 : g.b_cs == 1);
   if (va && vb) gemm_launch<WM, WN, AK, BK, true, true>(g, total, s);
   else if (va) gemm_launch<WM, WN, AK, BK, true, false>(g, total, s);
   else if (vb) gemm_launch<WM, WN, AK, BK, false, true>(g, total, s);
@@ -747,12 +790,15 @@ hipError_t t_gemm(const TGemm& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nbatch <= 0) return hipSuccess;
   if (g.ksplit > 0 && (g.beta != 1.f || g.bias || g.R || g.relu || g.mask || g.ksplit % GK)) return hipErrorInvalidValue;
   if (g.colsum && g.nbatch != 1) return hipErrorInvalidValue;
+  // a tile's byte offsets are 32-bit (at most 128 rows and 32 k values of either operand)
+  for (long long st : {g.a_rs, g.a_cs, g.b_rs, g.b_cs})
+    if (st < 0 || st > (1 << 21)) return hipErrorInvalidValue;
   const int nk = g.ksplit > 0 ? (g.K + g.ksplit - 1) / g.ksplit : 1;
   const long long total = (long long)g.nbatch * nk;
   if (g.M <= 32 && g.N <= 32 && g.ksplit == 0 && !g.colsum) {
     const bool ak = g.a_cs == 1 && g.a_rs != 1, bk = g.b_rs == 1 && g.b_cs != 1;
-    const bool va = vec4(g.A, ak ? g.a_rs : g.a_cs, g.a_b1, g.a_b2) && (ak ? g.a_cs == 1 : g.a_rs == 1);
-    const bool vb = vec4(g.B, bk ? g.b_cs : g.b_rs, g.b_b1, g.b_b2) && (bk ? g.b_rs == 1 : g.b_cs == 1);
+    const bool va = vec4(g.A, ak ? g.a_rs : g.a_cs, g.a_b1, g.a_b2, ak ? g.K : g.M) && (ak ? g.a_cs == 1 : g.a_rs == 1);
+    const bool vb = vec4(g.B, bk ? g.b_cs : g.b_rs, g.b_b1, g.b_b2, bk ? g.K : g.N) && (bk ? g.b_rs == 1 : g.b_cs == 1);
     for (long long z0 = 0; z0 < total; z0 += 4LL * 65535) {
       const unsigned nblk = (unsigned)std::min<long long>(65535, (total - z0 + 3) / 4);
       small_launch(ak, bk, va, vb, g, nblk, (int)z0, s);

@@ -212,3 +212,16 @@ def test_three_layers():
     c = gen.config(1, B=2, T=14, K=5, L=4, M=22, n_layers=3, dtype="f32")
     W, I = gen.make_weights(c), gen.make_inputs(c)
     check(c, W, I, _relevance(c), "mse")
+
+
+@pytest.mark.parametrize("d, heads, B, T, K, L, M", [
+    (32, 1, 1, 1, 1, 1, 1),        # one row everywhere: products of one row, one column, one k value
+    (32, 1, 1, 63, 31, 2, 33),     # one row below a 64-row tile, one value around a 32-deep k step
+    (64, 2, 1, 65, 33, 3, 64),     # one row above a tile and a step; an exact tile
+    (64, 1, 3, 43, 11, 5, 29),     # 129 context rows: a weight gradient's last row chunk of one row
+])
+def test_product_edges(d, heads, B, T, K, L, M):
+    """Edges of the product kernel's tiles (64 rows and columns, k steps of 32, row chunks of 64)."""
+    c = gen.config(1, B=B, T=T, K=K, L=L, M=M, d=d, n_heads=heads, ffn=4 * d, n_layers=1, dtype="f32")
+    W, I = gen.make_weights(c), gen.make_inputs(c)
+    check(c, W, I, _relevance(c), "mse")
