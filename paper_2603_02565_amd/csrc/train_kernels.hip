@@ -23,7 +23,6 @@ namespace {
 // both orientations.
 // ------------------------------------------------------------------------------------------
 constexpr int GK = 32;
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // One operand's tile of T rows (i or j) by GK k values, through registers into LDS.
 //   KC:  k contiguous in memory -> LDS [row][k], rows of GK + 4 floats (a wave half's 16-byte reads of

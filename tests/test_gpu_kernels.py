@@ -3,10 +3,12 @@ two sides of a dispatch line), as whole passes against the float64 oracle.  Tole
 harness's, per tensor and request."""
 import numpy as np
 import pytest
+import torch
 
 import gen
 import oracle
-from tests.gpu_harness import min_argmax, normwise, rtol_for, run_pass
+from paper_2603_02565_amd import flasheval as fe
+from tests.gpu_harness import make_evaluator, min_argmax, normwise, rtol_for, run_pass
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +47,36 @@ def check_pass(c):
 ])
 def test_wide_products(B, T, K, L, ffn):
     check_pass(gen.config(4, B=B, T=T, K=K, L=L, ffn=ffn, n_layers=1, vocab=600, M=600))
+
+
+@pytest.mark.parametrize("d,H,B,T", [
+    (128, 4, 1, 257),     # one query tile per wave; a last chunk of one key
+    (128, 2, 1, 300),     # head width 64
+    (128, 2, 64, 383),    # head width 64, two tiles per wave
+    (256, 8, 16, 513),    # two tiles per wave
+    (128, 4, 64, 520),    # eight tiles per wave, the last ones without queries
+])
+def test_attention_reference_moves(d, H, B, T):
+    """Peaked scores (queries and keys 25 times the usual size: a row's scores differ by up to 2^100
+    in weight), so the softmax reference of the chunked attention moves in later chunks.  The
+    context is encoded twice, its rows in the opposite order the second time: each row meets the
+    keys in the other order, so its reference moves elsewhere, and its result is the same but for
+    the bf16 rounding of probabilities and output (2^-9 each and side, in front of a residual
+    stream of the same size; the harness's 2e-2 is four times that)."""
+    c = gen.config(1, B=B, T=T, d=d, n_heads=H, ffn=4 * d, n_layers=1)
+    W = dict(gen.make_weights(c))
+    w = W["ctx.0.wqkv"].copy()
+    w[:, : 2 * d] *= 25
+    w[:, 2 * d:] *= 4
+    W["ctx.0.wqkv"] = w
+    W["ctx.0.wo"] = W["ctx.0.wo"] * 4
+    ev = make_evaluator(c, W)
+    x = torch.from_numpy(gen.make_inputs(c)["x"]).cuda().bfloat16()
+    kv = []
+    for rows in (x, x.flip(1).contiguous()):
+        bufs = ev.allocate(c.B, c.T, c.M, c.K, c.L)
+        fe.fe_encode_context(ev.handle, c.B, c.T, rows, None, bufs["kv"], bufs["ws"])
+        kv.append(bufs["kv"].float().view(2, B, T, d))
+    a, b = kv[0], kv[1].flip(2)
+    assert torch.isfinite(a).all()
+    assert (a - b).abs().max() <= rtol_for(c) * a.abs().max()
