@@ -80,3 +80,14 @@ def test_attention_reference_moves(d, H, B, T):
     a, b = kv[0], kv[1].flip(2)
     assert torch.isfinite(a).all()
     assert (a - b).abs().max() <= rtol_for(c) * a.abs().max()
+
+
+@pytest.mark.parametrize("d,H,B,T,M,K,L,ffn", [
+    (32, 1, 1, 1, 5, 1, 1, 32),       # one row; a step of 32 k values
+    (64, 1, 1, 65, 63, 9, 6, 160),    # one row above a tile; k = 160: a short second step
+    (128, 4, 2, 64, 40, 33, 3, 128),  # exact tiles and steps, padded item rows
+    (256, 4, 1, 63, 20, 7, 4, 288),   # LayerNorm rows of two steps
+    (512, 8, 1, 20, 70, 5, 13, 64),   # LayerNorm rows of four steps
+])
+def test_fp32_products(d, H, B, T, M, K, L, ffn):
+    check_pass(gen.config(1, B=B, T=T, M=M, K=K, L=L, d=d, n_heads=H, ffn=ffn, n_layers=2, dtype="f32"))
