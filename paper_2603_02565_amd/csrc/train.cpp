@@ -5,7 +5,7 @@
 // Every request of the batch goes through each operation at once: a module's rows are laid out as
 // sequences of equal length (context: B x T; item set: B x U_cap, the first n_uniq rows valid;
 // SeqEnc: B K x (L+1); cross-sequence: B x K), projections are single products over all rows,
-// attention is a batched product over (sequence, head) pairs with the padded keys and queries of
+// attention runs per (sequence, head) with the padded keys and queries of
 // the item set masked, and weight gradients sum over all rows.
 #include <cmath>
 #include <cstdarg>
@@ -115,12 +115,14 @@ struct Dims {
 // saved activations of one encoder block (pre-LN self-attention + FFN)
 struct EncAct {
   const float* x;                 // block input [R][d]
-  float *h1, *m1, *r1, *qkv, *P, *o, *x2, *h2, *m2, *r2, *a1, *y;   // a1 = relu(h2 W1 + b1)
+  float *h1, *m1, *r1, *qkv, *o, *x2, *h2, *m2, *r2, *a1, *y;   // a1 = relu(h2 W1 + b1)
+  float2* st;                     // attention statistics [nseq][H][S]
 };
 // saved activations of one item-set layer (self-attention, cross-attention to the context, FFN)
 struct ItemAct {
   const float* x;
-  float *h1, *m1, *r1, *qkv, *P, *o, *x2, *h2, *m2, *r2, *q, *Pc, *oc, *x3, *h3, *m3, *r3, *a1, *y;
+  float *h1, *m1, *r1, *qkv, *o, *x2, *h2, *m2, *r2, *q, *oc, *x3, *h3, *m3, *r3, *a1, *y;
+  float2 *st, *stc;               // statistics of both attentions [B][H][U]
   float *Kl, *Vl;                 // keys and values of the context for this layer [B][T][d]
 };
 // one encoder stack: nseq sequences of S rows and the final LayerNorm
@@ -143,7 +145,7 @@ struct Plan {
   float *item_out, *item_mf, *item_rf;
   float *scores, *dscores;
   // backward scratch
-  float *dx_ctx, *dx_item, *dx_seq, *dx_cross, *dQc, *dH, *dCp, *tF, *td, *tq, *dqkv, *dP, *dKl, *dVl;
+  float *dx_ctx, *dx_item, *dx_seq, *dx_cross, *dQc, *dH, *dCp, *tF, *td, *tq, *dqkv, *dKl, *dVl;
 };
 
 void plan_enc_stack(Arena& A, Stack& st, const Dims& D, int nseq, int S, const int32_t* valid, bool first_row_only) {
@@ -158,7 +160,7 @@ void plan_enc_stack(Arena& A, Stack& st, const Dims& D, int nseq, int S, const i
     a.x = nullptr;
     a.h1 = A.get<float>(R * d); a.m1 = A.get<float>(R); a.r1 = A.get<float>(R);
     a.qkv = A.get<float>(R * 3 * d);
-    a.P = A.get<float>((size_t)nseq * D.H * S * S);
+    a.st = A.get<float2>((size_t)nseq * D.H * S);
     a.o = A.get<float>(R * d); a.x2 = A.get<float>(R * d);
     a.h2 = A.get<float>(R * d); a.m2 = A.get<float>(R); a.r2 = A.get<float>(R);
     a.a1 = A.get<float>(R * F);
@@ -189,11 +191,11 @@ Plan make_plan(Arena& A, const Dims& D) {
     a.x = nullptr;
     a.h1 = A.get<float>(R * d); a.m1 = A.get<float>(R); a.r1 = A.get<float>(R);
     a.qkv = A.get<float>(R * 3 * d);
-    a.P = A.get<float>(B * D.H * U * U);
+    a.st = A.get<float2>(B * D.H * U);
     a.o = A.get<float>(R * d); a.x2 = A.get<float>(R * d);
     a.h2 = A.get<float>(R * d); a.m2 = A.get<float>(R); a.r2 = A.get<float>(R);
     a.q = A.get<float>(R * d);
-    a.Pc = A.get<float>(B * D.H * U * T);
+    a.stc = A.get<float2>(B * D.H * U);
     a.oc = A.get<float>(R * d); a.x3 = A.get<float>(R * d);
     a.h3 = A.get<float>(R * d); a.m3 = A.get<float>(R); a.r3 = A.get<float>(R);
     a.a1 = A.get<float>(R * F);
@@ -211,8 +213,6 @@ Plan make_plan(Arena& A, const Dims& D) {
   // backward scratch: sized for the largest module
   const size_t Rc = B * T, Rs = B * K * S, Rx = B * K;
   const size_t Rmax = std::max(std::max(Rc, R), std::max(Rs, Rx));
-  const size_t Pmax = std::max(std::max(B * D.H * T * T, B * D.H * U * std::max(U, T)),
-                               std::max(B * K * D.H * S * S, B * D.H * K * K));
   p.dx_ctx = A.get<float>(Rc * d);
   p.dx_item = A.get<float>(R * d);
   p.dx_seq = A.get<float>(Rs * d);
@@ -224,7 +224,6 @@ Plan make_plan(Arena& A, const Dims& D) {
   p.td = A.get<float>(Rmax * d);
   p.tq = A.get<float>(R * d);
   p.dqkv = A.get<float>(Rmax * 3 * d);
-  p.dP = A.get<float>(Pmax);
   p.dKl = A.get<float>(Rc * d);
   p.dVl = A.get<float>(Rc * d);
   return p;
@@ -236,8 +235,6 @@ Plan make_plan(Arena& A, const Dims& D) {
 TGemm gemm0() {
   TGemm g;
   std::memset(&g, 0, sizeof g);
-  g.nbatch = 1;
-  g.nb2 = 1;
   g.alpha = 1.f;
   return g;
 }
@@ -290,85 +287,32 @@ hipError_t linear_dw(const float* X, long long x_rs, int R, int din, const float
   return t_gemm(g, s);
 }
 
-// Multi-head attention over nseq sequences, all heads at once.  Query rows of sequence z start at
-// q + z*q_bs (row stride q_rs, head h in columns h*dh..), likewise keys and values; Sq queries and
-// Sk keys per sequence; P [nseq][H][Sq][Sk]; o rows at o + z*o_bs (stride o_rs).
-struct AttnIO {
-  const float *q, *k, *v;
-  long long q_rs, k_rs, v_rs, q_bs, k_bs, v_bs;
-  int nseq, Sq, Sk;
-  const int32_t *qlen, *klen;
-};
-
-hipError_t attn_fwd(const AttnIO& a, const Dims& D, float* P, float* o, long long o_rs, long long o_bs, hipStream_t s) {
-  const long long pz = (long long)a.Sq * a.Sk;
-  TGemm g = gemm0();
-  g.A = a.q; g.a_rs = a.q_rs; g.a_cs = 1; g.a_b1 = a.q_bs; g.a_b2 = D.dh;
-  g.B = a.k; g.b_rs = 1; g.b_cs = a.k_rs; g.b_b1 = a.k_bs; g.b_b2 = D.dh;
-  g.C = P; g.c_rs = a.Sk; g.c_b1 = D.H * pz; g.c_b2 = pz;
-  g.M = a.Sq; g.N = a.Sk; g.K = D.dh;
-  g.nbatch = a.nseq * D.H; g.nb2 = D.H;
-  TRY(t_gemm(g, s));
-  TRY(t_softmax_fwd(P, P, a.nseq * D.H, D.H, a.Sq, a.Sk, 1.f / std::sqrt((float)D.dh), a.qlen, a.klen, s));
-  TGemm h = gemm0();
-  h.A = P; h.a_rs = a.Sk; h.a_cs = 1; h.a_b1 = D.H * pz; h.a_b2 = pz;
-  h.B = a.v; h.b_rs = a.v_rs; h.b_cs = 1; h.b_b1 = a.v_bs; h.b_b2 = D.dh;
-  h.C = o; h.c_rs = o_rs; h.c_b1 = o_bs; h.c_b2 = D.dh;
-  h.M = a.Sq; h.N = D.dh; h.K = a.Sk;
-  h.nbatch = a.nseq * D.H; h.nb2 = D.H;
-  return t_gemm(h, s);
-}
-
-// dq, dk, dv (overwritten; same strides as q, k, v) from dO and the saved P; dP is scratch.
-hipError_t attn_bwd(const AttnIO& a, const Dims& D, const float* P, const float* dO, long long do_rs, long long do_bs,
-                    float* dq, float* dk, float* dv, float* dP, hipStream_t s) {
-  const long long pz = (long long)a.Sq * a.Sk;
-  const int nb = a.nseq * D.H;
-  // dP = dO V^T
-  TGemm g = gemm0();
-  g.A = dO; g.a_rs = do_rs; g.a_cs = 1; g.a_b1 = do_bs; g.a_b2 = D.dh;
-  g.B = a.v; g.b_rs = 1; g.b_cs = a.v_rs; g.b_b1 = a.v_bs; g.b_b2 = D.dh;
-  g.C = dP; g.c_rs = a.Sk; g.c_b1 = D.H * pz; g.c_b2 = pz;
-  g.M = a.Sq; g.N = a.Sk; g.K = D.dh;
-  g.nbatch = nb; g.nb2 = D.H;
-  TRY(t_gemm(g, s));
-  // dV = P^T dO
-  g = gemm0();
-  g.A = P; g.a_rs = 1; g.a_cs = a.Sk; g.a_b1 = D.H * pz; g.a_b2 = pz;
-  g.B = dO; g.b_rs = do_rs; g.b_cs = 1; g.b_b1 = do_bs; g.b_b2 = D.dh;
-  g.C = dv; g.c_rs = a.v_rs; g.c_b1 = a.v_bs; g.c_b2 = D.dh;
-  g.M = a.Sk; g.N = D.dh; g.K = a.Sq;
-  g.nbatch = nb; g.nb2 = D.H;
-  TRY(t_gemm(g, s));
-  // dS = scale P (dP - rowsum(P dP))
-  TRY(t_softmax_bwd(P, dP, (long long)nb * a.Sq, a.Sk, 1.f / std::sqrt((float)D.dh), s));
-  // dQ = dS K
-  g = gemm0();
-  g.A = dP; g.a_rs = a.Sk; g.a_cs = 1; g.a_b1 = D.H * pz; g.a_b2 = pz;
-  g.B = a.k; g.b_rs = a.k_rs; g.b_cs = 1; g.b_b1 = a.k_bs; g.b_b2 = D.dh;
-  g.C = dq; g.c_rs = a.q_rs; g.c_b1 = a.q_bs; g.c_b2 = D.dh;
-  g.M = a.Sq; g.N = D.dh; g.K = a.Sk;
-  g.nbatch = nb; g.nb2 = D.H;
-  TRY(t_gemm(g, s));
-  // dK = dS^T Q
-  g = gemm0();
-  g.A = dP; g.a_rs = 1; g.a_cs = a.Sk; g.a_b1 = D.H * pz; g.a_b2 = pz;
-  g.B = a.q; g.b_rs = a.q_rs; g.b_cs = 1; g.b_b1 = a.q_bs; g.b_b2 = D.dh;
-  g.C = dk; g.c_rs = a.k_rs; g.c_b1 = a.k_bs; g.c_b2 = D.dh;
-  g.M = a.Sk; g.N = D.dh; g.K = a.Sq;
-  g.nbatch = nb; g.nb2 = D.H;
-  return t_gemm(g, s);
+TAttn attn0(const Dims& D, float2* stat, float* o, int S) {
+  TAttn a;
+  std::memset(&a, 0, sizeof a);
+  a.H = D.H; a.dh = D.dh;
+  a.scale = 1.f / std::sqrt((float)D.dh);
+  a.o = o; a.o_rs = D.d; a.o_bs = (long long)S * D.d;
+  a.stat = stat;
+  return a;
 }
 
 // self-attention of the rows of a qkv buffer [nseq][S][3d]
-AttnIO self_io(const float* qkv, const Dims& D, int nseq, int S, const int32_t* valid) {
-  AttnIO a;
+TAttn self_attn(const float* qkv, const Dims& D, int nseq, int S, const int32_t* valid, float2* stat, float* o) {
+  TAttn a = attn0(D, stat, o, S);
   const long long rs = 3LL * D.d;
   a.q = qkv; a.k = qkv + D.d; a.v = qkv + 2 * D.d;
   a.q_rs = a.k_rs = a.v_rs = rs;
   a.q_bs = a.k_bs = a.v_bs = rs * S;
   a.nseq = nseq; a.Sq = a.Sk = S;
   a.qlen = a.klen = valid;
+  return a;
+}
+
+// its backward from dO (rows as o): dqkv as qkv
+TAttn self_attn_bwd(TAttn a, const Dims& D, const float* dO, float* dqkv) {
+  a.dO = dO; a.do_rs = a.o_rs; a.do_bs = a.o_bs;
+  a.dq = dqkv; a.dk = dqkv + D.d; a.dv = dqkv + 2 * D.d;
   return a;
 }
 
@@ -380,7 +324,7 @@ hipError_t enc_fwd(const float* W, const EncP& p, EncAct& a, const Dims& D, int 
   const int R = nseq * S, d = D.d, F = D.F;
   TRY(t_ln_fwd(a.x, d, R, d, W + p.ln1g, W + p.ln1b, a.h1, d, a.m1, a.r1, s));
   TRY(linear(a.h1, d, R, d, W + p.wqkv, W + p.bqkv, 3 * d, a.qkv, 3 * d, nullptr, false, s));
-  TRY(attn_fwd(self_io(a.qkv, D, nseq, S, valid), D, a.P, a.o, d, (long long)S * d, s));
+  TRY(t_attn_fwd(self_attn(a.qkv, D, nseq, S, valid, a.st, a.o), s));
   TRY(linear(a.o, d, R, d, W + p.wo, W + p.bo, d, a.x2, d, a.x, false, s));
   TRY(t_ln_fwd(a.x2, d, R, d, W + p.ln2g, W + p.ln2b, a.h2, d, a.m2, a.r2, s));
   TRY(linear(a.h2, d, R, d, W + p.w1, W + p.b1, F, a.a1, F, nullptr, true, s));
@@ -400,8 +344,7 @@ hipError_t enc_bwd(const float* W, float* G, const EncP& p, const EncAct& a, con
   // self-attention
   TRY(linear_dw(a.o, d, R, d, dx, d, d, G + p.wo, G + p.bo, s));
   TRY(linear_dx(dx, d, R, d, W + p.wo, d, pl.td, d, false, nullptr, s));
-  const AttnIO io = self_io(a.qkv, D, nseq, S, valid);
-  TRY(attn_bwd(io, D, a.P, pl.td, d, (long long)S * d, pl.dqkv, pl.dqkv + d, pl.dqkv + 2 * d, pl.dP, s));
+  TRY(t_attn_bwd(self_attn_bwd(self_attn(a.qkv, D, nseq, S, valid, a.st, a.o), D, pl.td, pl.dqkv), s));
   TRY(linear_dw(a.h1, d, R, d, pl.dqkv, 3 * d, 3 * d, G + p.wqkv, G + p.bqkv, s));
   TRY(linear_dx(pl.dqkv, 3 * d, R, 3 * d, W + p.wqkv, d, pl.td, d, false, nullptr, s));
   return t_ln_bwd(a.x, d, R, d, W + p.ln1g, a.m1, a.r1, pl.td, d, dx, d, G + p.ln1g, G + p.ln1b, s);
@@ -439,14 +382,13 @@ hipError_t stack_bwd(const float* W, float* G, const std::vector<EncP>& ps, size
 // Item-set layer (Section 4.2): set self-attention, cross-attention of the items to the encoded
 // context through this layer's key/value projections, FFN; all pre-LN with residuals
 // ------------------------------------------------------------------------------------------
-AttnIO cross_io(const ItemAct& a, const Dims& D, const int32_t* n_uniq) {
-  AttnIO io;
+TAttn cross_attn(const ItemAct& a, const Dims& D, const int32_t* n_uniq) {
+  TAttn io = attn0(D, a.stc, a.oc, D.U);
   io.q = a.q; io.q_rs = D.d; io.q_bs = (long long)D.U * D.d;
   io.k = a.Kl; io.k_rs = D.d; io.k_bs = (long long)D.T * D.d;
   io.v = a.Vl; io.v_rs = D.d; io.v_bs = (long long)D.T * D.d;
   io.nseq = D.B; io.Sq = D.U; io.Sk = D.T;
   io.qlen = n_uniq;
-  io.klen = nullptr;
   return io;
 }
 
@@ -457,11 +399,11 @@ hipError_t item_fwd(const float* W, const ItemP& p, const KvP& kv, ItemAct& a, c
   TRY(linear(Qc, d, Rc, d, W + kv.wv, W + kv.bv, d, a.Vl, d, nullptr, false, s));
   TRY(t_ln_fwd(a.x, d, R, d, W + p.ln1g, W + p.ln1b, a.h1, d, a.m1, a.r1, s));
   TRY(linear(a.h1, d, R, d, W + p.wqkv, W + p.bqkv, 3 * d, a.qkv, 3 * d, nullptr, false, s));
-  TRY(attn_fwd(self_io(a.qkv, D, D.B, D.U, n_uniq), D, a.P, a.o, d, (long long)D.U * d, s));
+  TRY(t_attn_fwd(self_attn(a.qkv, D, D.B, D.U, n_uniq, a.st, a.o), s));
   TRY(linear(a.o, d, R, d, W + p.wo, W + p.bo, d, a.x2, d, a.x, false, s));
   TRY(t_ln_fwd(a.x2, d, R, d, W + p.ln2g, W + p.ln2b, a.h2, d, a.m2, a.r2, s));
   TRY(linear(a.h2, d, R, d, W + p.wq, W + p.bq, d, a.q, d, nullptr, false, s));
-  TRY(attn_fwd(cross_io(a, D, n_uniq), D, a.Pc, a.oc, d, (long long)D.U * d, s));
+  TRY(t_attn_fwd(cross_attn(a, D, n_uniq), s));
   TRY(linear(a.oc, d, R, d, W + p.wo2, W + p.bo2, d, a.x3, d, a.x2, false, s));
   TRY(t_ln_fwd(a.x3, d, R, d, W + p.ln3g, W + p.ln3b, a.h3, d, a.m3, a.r3, s));
   TRY(linear(a.h3, d, R, d, W + p.w1, W + p.b1, F, a.a1, F, nullptr, true, s));
@@ -481,7 +423,10 @@ hipError_t item_bwd(const float* W, float* G, const ItemP& p, const KvP& kv, con
   // cross-attention to the context
   TRY(linear_dw(a.oc, d, R, d, dx, d, d, G + p.wo2, G + p.bo2, s));
   TRY(linear_dx(dx, d, R, d, W + p.wo2, d, pl.td, d, false, nullptr, s));
-  TRY(attn_bwd(cross_io(a, D, n_uniq), D, a.Pc, pl.td, d, (long long)D.U * d, pl.tq, pl.dKl, pl.dVl, pl.dP, s));
+  TAttn ca = cross_attn(a, D, n_uniq);
+  ca.dO = pl.td; ca.do_rs = ca.o_rs; ca.do_bs = ca.o_bs;
+  ca.dq = pl.tq; ca.dk = pl.dKl; ca.dv = pl.dVl;
+  TRY(t_attn_bwd(ca, s));
   TRY(linear_dw(a.h2, d, R, d, pl.tq, d, d, G + p.wq, G + p.bq, s));
   TRY(linear_dx(pl.tq, d, R, d, W + p.wq, d, pl.td, d, false, nullptr, s));
   TRY(t_ln_bwd(a.x2, d, R, d, W + p.ln2g, a.m2, a.r2, pl.td, d, dx, d, G + p.ln2g, G + p.ln2b, s));
@@ -492,8 +437,7 @@ hipError_t item_bwd(const float* W, float* G, const ItemP& p, const KvP& kv, con
   // set self-attention
   TRY(linear_dw(a.o, d, R, d, dx, d, d, G + p.wo, G + p.bo, s));
   TRY(linear_dx(dx, d, R, d, W + p.wo, d, pl.td, d, false, nullptr, s));
-  TRY(attn_bwd(self_io(a.qkv, D, D.B, D.U, n_uniq), D, a.P, pl.td, d, (long long)D.U * d, pl.dqkv, pl.dqkv + d,
-               pl.dqkv + 2 * d, pl.dP, s));
+  TRY(t_attn_bwd(self_attn_bwd(self_attn(a.qkv, D, D.B, D.U, n_uniq, a.st, a.o), D, pl.td, pl.dqkv), s));
   TRY(linear_dw(a.h1, d, R, d, pl.dqkv, 3 * d, 3 * d, G + p.wqkv, G + p.bqkv, s));
   TRY(linear_dx(pl.dqkv, 3 * d, R, 3 * d, W + p.wqkv, d, pl.td, d, false, nullptr, s));
   return t_ln_bwd(a.x, d, R, d, W + p.ln1g, a.m1, a.r1, pl.td, d, dx, d, G + p.ln1g, G + p.ln1b, s);

@@ -12,9 +12,8 @@ fe_status fe_report(fe_status st, const char* msg);
 enum { TRAIN_MSE = 0, TRAIN_BCE = 1, TRAIN_CE = 2 };
 constexpr int TRAIN_COL_ROWS = 64;   // rows per workgroup of a column reduction
 
-// C[z] = alpha * A[z] B[z] + beta * C[z] + bias (bias[j] over columns, may be null), z < nbatch,
-// z = z1 * nb2 + z2.  Element (i, k) of A[z] is A[z1*a_b1 + z2*a_b2 + i*a_rs + k*a_cs]; B (k, j)
-// and C (i, j) likewise (C with unit column stride).  ksplit > 0: the K range is cut into chunks
+// C = alpha * A B + beta * C + bias (bias[j] over columns, may be null).  Element (i, k) of A is
+// A[i*a_rs + k*a_cs]; B (k, j) and C (i, j) likewise (C with unit column stride).  ksplit > 0: the K range is cut into chunks
 // of ksplit (a multiple of 32) and each chunk adds alpha * its partial product into C atomically (beta must be 1,
 // bias and the epilogue null); the sum order then varies from run to run.
 struct TGemm {
@@ -27,13 +26,11 @@ struct TGemm {
   const float* R;
   int relu;
   const float* mask;
-  // colsum (k_gemm only, nbatch 1): colsum[j] += alpha * sum_k B[k][j] over this launch's k range (the
+  // colsum: colsum[j] += alpha * sum_k B[k][j] over this launch's k range (the
   // bias gradient when B is dY and k runs over rows); null: not computed.
   float* colsum;
   int M, N, K;
   long long a_rs, a_cs, b_rs, b_cs, c_rs;
-  long long a_b1, a_b2, b_b1, b_b2, c_b1, c_b2;
-  int nbatch, nb2;
   float alpha, beta;
   int ksplit;
 };
@@ -46,12 +43,26 @@ hipError_t t_ln_fwd(const float* X, long long x_rs, int rows, int d, const float
 hipError_t t_ln_bwd(const float* X, long long x_rs, int rows, int d, const float* g, const float* mean,
                     const float* rstd, const float* dY, long long dy_rs, float* dX, long long dx_rs, float* dg,
                     float* db, hipStream_t s);
-// P = softmax(scale * S) per row of nk keys; rows of batch z (z1 = z / nb2) use keys j < klen[z1]
-// and are zero for query rows i >= qlen[z1] (null: no bound)
-hipError_t t_softmax_fwd(const float* S, float* P, int nbatch, int nb2, int nq, int nk, float scale,
-                         const int32_t* qlen, const int32_t* klen, hipStream_t s);
-// dP <- scale * P * (dP - rowsum(P * dP)): the gradient of the pre-scale scores, in place
-hipError_t t_softmax_bwd(const float* P, float* dP, long long rows, int nk, float scale, hipStream_t s);
+// Multi-head attention over nseq sequences: query rows of sequence z start at q + z*q_bs (row stride
+// q_rs, head h in columns h*dh..), likewise keys, values, o and dO; Sq queries and Sk keys per
+// sequence, of which the first qlen[z] and klen[z] count (null: all; queries past them give zero
+// rows).  Forward: o = softmax(scale q k^T) v, stat [nseq][H][Sq] (the backward reads both).
+// Backward: dq, dk, dv (overwritten; strides of q, k, v) from dO.  dh is 32 or 64.
+struct TAttn {
+  const float *q, *k, *v;
+  long long q_rs, k_rs, v_rs, q_bs, k_bs, v_bs;
+  int nseq, H, dh, Sq, Sk;
+  const int32_t *qlen, *klen;
+  float scale;
+  float* o;
+  long long o_rs, o_bs;
+  float2* stat;
+  const float* dO;
+  long long do_rs, do_bs;
+  float *dq, *dk, *dv;
+};
+hipError_t t_attn_fwd(const TAttn& a, hipStream_t s);
+hipError_t t_attn_bwd(const TAttn& a, hipStream_t s);
 hipError_t t_copy(const float* x, float* y, long long n, hipStream_t s);
 hipError_t t_fill(float* y, long long n, float v, hipStream_t s);
 // Y[b][r] = row idx[b*idx_bs + r] of the table at T + b*t_bs, for r < nvalid[b] (all rows if null)

@@ -1,7 +1,7 @@
 // fp32 kernels of the training step (Section 4.5): the forward with saved activations and its
-// backward.  Plain, general kernels: a batched strided product, row-wise LayerNorm and softmax
-// with their backward passes, elementwise steps, row gathers and their scatter-add backward, and
-// the losses with the label construction of Appendix B.1.
+// backward: a strided product, attention per (sequence, head), row-wise LayerNorm, all with their
+// backward passes, elementwise steps, row gathers and their scatter-add backward, and the losses
+// with the label construction of Appendix B.1.
 #include "fe_common.h"
 #include "train_kernels.h"
 
@@ -11,9 +11,8 @@
 namespace {
 
 // ------------------------------------------------------------------------------------------
-// C[z] = alpha * op(A[z]) op(B[z]) + beta * C[z] (+ bias[j]); element (i, k) of A[z] at
-// A + z1*a_b1 + z2*a_b2 + i*a_rs + k*a_cs (likewise B with (k, j), C with (i, j) and unit column
-// stride), z = z1*nb2 + z2.
+// C = alpha * op(A) op(B) + beta * C (+ bias[j]); element (i, k) of A at A + i*a_rs + k*a_cs (likewise
+// B with (k, j), C with (i, j) and unit column stride).
 //
 // fp32 matrix cores: a workgroup of four waves owns a (32 WM) x (32 WN) output tile, each wave one
 // 32 x 32 block accumulated by v_mfma_f32_32x32x2_f32 (lane l feeds A[l%32][l/32] and
@@ -25,12 +24,11 @@ namespace {
 constexpr int GK = 32;
 
 // One operand's tile of T rows (i or j) by GK k values, through registers into LDS.
-//   KC:  k contiguous in memory -> LDS [row][k], rows of GK + 4 floats (a wave half's 16-byte reads of
-//        32 rows fall on every bank group once);
-//   !KC: rows contiguous        -> LDS [k][row], rows of T + 8 floats (the two wave halves read k
-//        and k + 4, which lie 32 banks apart).
-// Either way the store keeps the orientation of the load, 16 bytes at a time (VEC).
-// MFMA c of the group of eight k values from 8s takes k = 8s + 4 (l/32) + c, for both operands.
+//   KC:  k contiguous in memory -> LDS [row][k], each group of eight k values as 0 2 4 6 1 3 5 7, rows of
+//        GK + 4 floats (a wave half's 16-byte reads of 32 rows fall on every bank group once);
+//   !KC: rows contiguous        -> LDS [k][row], rows of T + 8 floats.
+// Either way the store keeps the orientation of the load (VEC: four values of it at a time).  MFMA c
+// of the group of eight k values from 8s takes k = 8s + 2c + (l/32): k ascends over the MFMAs.
 template <int T, bool KC, bool VEC>
 struct TOperand {
   static constexpr int N = GK * T / 256;                    // values per thread and step
@@ -75,9 +73,20 @@ struct TOperand {
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
       const int e = threadIdx.x + 256 * q;
-      float* d = S + (KC ? (e / (GK / W)) * LD + W * (e % (GK / W)) : (e / (T / W)) * LD + W * (e % (T / W)));
-      if constexpr (VEC) *reinterpret_cast<float4*>(d) = make_float4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
-      else *d = r[q];
+      if constexpr (KC) {
+        const int k = W * (e % (GK / W));
+        float* d = S + (e / (GK / W)) * LD + k / 8 * 8 + k % 2 * 4 + k % 8 / 2;
+        if constexpr (VEC) {
+          *reinterpret_cast<float2*>(d) = make_float2(r[4 * q], r[4 * q + 2]);
+          *reinterpret_cast<float2*>(d + 4) = make_float2(r[4 * q + 1], r[4 * q + 3]);
+        } else {
+          *d = r[q];
+        }
+      } else {
+        float* d = S + (e / (T / W)) * LD + W * (e % (T / W));
+        if constexpr (VEC) *reinterpret_cast<float4*>(d) = make_float4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
+        else *d = r[q];
+      }
     }
   }
   // the lane's operands of the four MFMAs of k group s, for the 32 rows from w
@@ -88,7 +97,7 @@ struct TOperand {
       v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     } else {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) v[c] = S[(8 * s + 4 * lk + c) * LD + w + lr];
+      for (int c = 0; c < 4; ++c) v[c] = S[(8 * s + 2 * c + lk) * LD + w + lr];
     }
   }
 };
@@ -103,17 +112,15 @@ struct TOperand {
 // product 9.3 -> 4.2 us; 16384 x 384 x 128 25.8 -> 23.2 us (67 TFLOP/s; its output alone is 25 MB);
 // a training step of 385 context rows (d 64) 1984 -> 1390 us, of 16384 (d 128) 5632 -> 4962 us.
 template <int WM, int WN, bool AK, bool BK, bool VA, bool VB>
-__global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles_n, int tiles) {
+__global__ __launch_bounds__(256) void k_gemm(TGemm g, int kc0, int tiles_n, int tiles) {
   static_assert(WM * WN == 4, "four waves");
   constexpr int TM = 32 * WM, TN = 32 * WN;
   using OA = TOperand<TM, AK, VA>;
   using OB = TOperand<TN, BK, VB>;
   __shared__ __align__(16) float As[2][OA::SIZE];
   __shared__ __align__(16) float Bs[2][OB::SIZE];
-  const int id = xcd_tile(blockIdx.x, gridDim.x);   // tiles of one batch item (or k chunk) are neighbours
-  const int zz = z0 + id / tiles, tile = id % tiles;
-  const int z = zz % nz, kc = zz / nz;
-  const int z1 = z / g.nb2, z2 = z % g.nb2;
+  const int id = xcd_tile(blockIdx.x, gridDim.x);   // tiles of one k chunk are neighbours
+  const int kc = kc0 + id / tiles, tile = id % tiles;
   const int kbeg = g.ksplit > 0 ? kc * g.ksplit : 0;
   const int kend = g.ksplit > 0 ? min(g.K, kbeg + g.ksplit) : g.K;
   const int ti = tile / tiles_n, tj = tile % tiles_n;
@@ -123,8 +130,8 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles
   const int lr = lane & 31, lk = lane >> 5;
   OA a;
   OB b;
-  a.init(g.A + z1 * g.a_b1 + z2 * g.a_b2, i0, g.M, g.a_rs, g.a_cs);
-  b.init(g.B + z1 * g.b_b1 + z2 * g.b_b2, j0, g.N, g.b_cs, g.b_rs);
+  a.init(g.A, i0, g.M, g.a_rs, g.a_cs);
+  b.init(g.B, j0, g.N, g.b_cs, g.b_rs);
   auto load = [&](int k0) {
     a.load(k0, kend);
     b.load(k0, kend);
@@ -160,7 +167,7 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles
       const int jj = threadIdx.x % TN, part = threadIdx.x / TN;
       constexpr int KP = GK * TN / 256;
 #pragma unroll
-      for (int t = 0; t < KP; ++t) cs += BK ? Bc[jj * OB::LD + part * KP + t] : Bc[(part * KP + t) * OB::LD + jj];
+      for (int t = 0; t < KP; ++t) cs += BK ? Bc[jj * OB::LD + part * KP + t] : Bc[(part * KP + t) * OB::LD + jj];   // in either order of k
     }
     if (more) {
       a.store(As[cur ^ 1]);   // last read one step ago, before the barrier that ended it
@@ -181,8 +188,7 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles
   const int j = j0 + wj + lr;
   if (j >= g.N) return;
   const int ib = i0 + wi + 4 * lk;                  // row of accumulator 4q + e: ib + 8q + e
-  const long long zo = z1 * g.c_b1 + z2 * g.c_b2 + j;
-  float* C = g.C + zo;
+  float* C = g.C + j;
   if (g.ksplit > 0) {
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
@@ -200,7 +206,7 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles
   if (g.R) {
     float v[16];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) v[t] = g.R[zo + at(t)];
+    for (int t = 0; t < 16; ++t) v[t] = g.R[j + at(t)];
 #pragma unroll
     for (int t = 0; t < 16; ++t) r[t] += v[t];
   }
@@ -210,7 +216,7 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles
   if (g.mask) {
     float v[16];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) v[t] = g.mask[zo + at(t)];
+    for (int t = 0; t < 16; ++t) v[t] = g.mask[j + at(t)];
 #pragma unroll
     for (int t = 0; t < 16; ++t) r[t] = v[t] > 0.f ? r[t] : 0.f;
   }
@@ -228,140 +234,474 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int z0, int nz, int tiles
   }
 }
 
-// Batched products with M, N <= 32 (attention inside short sequences): each wave owns one batch
-// item's 32 x 32 tile, four items per workgroup, same k-steps and prefetch as k_gemm.
-template <bool AK, bool BK, bool VA, bool VB>
-__global__ __launch_bounds__(256) void k_gemm_small(TGemm g, int z0) {
-  constexpr int P = 36, N1 = GK * 32 / 64;   // elements per lane per operand per k-step
-  __shared__ __align__(16) float As[4][GK][P];
-  __shared__ __align__(16) float Bs[4][GK][P];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int z = z0 + blockIdx.x * 4 + wave;
-  const bool live = z < g.nbatch;
-  const int z1 = live ? z / g.nb2 : 0, z2 = live ? z % g.nb2 : 0;
-  const float* A = g.A + z1 * g.a_b1 + z2 * g.a_b2;
-  const float* B = g.B + z1 * g.b_b1 + z2 * g.b_b2;
-  float* C = g.C + z1 * g.c_b1 + z2 * g.c_b2;
-  const float* Rz = g.R + z1 * g.c_b1 + z2 * g.c_b2;
-  const float* Mz = g.mask + z1 * g.c_b1 + z2 * g.c_b2;
-  const int lr = lane & 31, lk = lane >> 5;
-  float ra[N1], rb[N1];
-  // VA / VB: four consecutive elements of the contiguous index per load (aligned, checked by the
-  // launcher); the registers hold the same N1 scalars either way
-  auto load = [&](int k0) {
-    if constexpr (VA) {
+// ------------------------------------------------------------------------------------------
+// Attention of the training step, forward and backward, per (sequence, head): scores and
+// probabilities stay on chip.  The forward keeps each query's maximum m and 1 / l of its normaliser
+// l = sum exp(score - m) (infinity and 0 for a query that attends to nothing), from which the
+// backward forms the forward's probabilities again.
+//
+// Everything is a product of TS x TS blocks on the fp32 matrix cores (TS = 32: 32x32x2, TS = 16:
+// 16x16x4; NS = 64 / TS k slots).  Accumulator a of a lane in slot g is block row
+// 4 NS (a / 4) + 4 g + a % 4 of column lane % TS.  A product's left rows are fed in the order that
+// makes it row NS a + g of the LDS tile: read as a k index, that is what a lane of slot g feeds to
+// product a of a following contraction over the block's rows, so a block of probabilities goes into
+// the next product from its registers.  Contractions over the head's columns take column
+// 4 NS s + NS c + g for product (s, c), which a tile's column order (pos) makes 16-byte reads.
+//
+// The forward's sums run in a fixed order whatever the tiling (k ascending over the products; the
+// normaliser as a tree over the key index: 64-strided partial sums, then bits 5 to 0), with the
+// maximum known before the first exponential: a ReLU further on turns a rounding difference at zero
+// into a jump of the gradient, so the order is part of the result.
+//
+// A wave owns TS queries (forward, dQ: blocks are [key][query]) or TS keys (dK and dV: blocks are
+// [query][key]) and walks the other side in tiles that the workgroup stages in LDS, the next tile's
+// loads in flight; sequences of up to TS rows (SMALL) take one wave each instead.  Bound by the fp32
+// matrix rate (2 products forward, 7 backward: S and dP are formed in both orientations, which costs
+// less than moving dS through memory or adding dQ atomically).  Measured, before (probabilities
+// through memory, a launch per product) and after: 256 x 256, 256 heads of 32: forward 69 -> 32 us,
+// backward 117 -> 79 us; 11 x 11, 12800 heads of 32: forward 62 -> 18 us, backward 118 -> 32 us; 77 x
+// 77, 10 heads of 32: forward 16 -> 12 us, backward 33 -> 15 us.
+// ------------------------------------------------------------------------------------------
+// LDS written before it by any lane of the wave is visible to the wave's reads after it.
+FE_DEV void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int TS>
+FE_DEV float slot_max(float v) {
+  if constexpr (TS == 16) return rows_max(v);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int TS>
+FE_DEV float slot_sum(float v) {
+  if constexpr (TS == 16) return rows_sum(v);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Sum over the keys of a column: p0 and p1 hold the sums over the even and odd tiles (accumulator i,
+// slot g: key NS i + g of a tile; TS = 16 has one tile, whose bits 5 and 4 add nothing).
+template <int TS, class Acc>
+FE_DEV float tree_sum(const Acc& p0, const Acc& p1) {
+  constexpr int NA = TS * TS / 64;
+  float x[NA];
 #pragma unroll
-      for (int q = 0; q < N1 / 4; ++q) {
-        const int e = lane + 64 * q;
-        const int i = AK ? e / (GK / 4) : 4 * (e % 8), k = AK ? k0 + 4 * (e % (GK / 4)) : k0 + e / 8;
-        const float* src = A + i * g.a_rs + k * g.a_cs;
-        if (live && (AK ? (i < g.M && k + 3 < g.K) : (i + 3 < g.M && k < g.K))) {
-          const float4 v = *reinterpret_cast<const float4*>(src);
-          ra[4 * q] = v.x; ra[4 * q + 1] = v.y; ra[4 * q + 2] = v.z; ra[4 * q + 3] = v.w;
-        } else {
+  for (int i = 0; i < NA; ++i) x[i] = p0[i] + p1[i];
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            ra[4 * q + c] = (live && (AK ? (i < g.M && k + c < g.K) : (i + c < g.M && k < g.K))) ? src[AK ? c : c * g.a_rs] : 0.f;
-        }
-      }
-    } else {
+  for (int h = NA / 2; h > 0; h >>= 1)
 #pragma unroll
-      for (int t = 0; t < N1; ++t) {
-        const int e = lane + 64 * t;
-        const int kk = AK ? e % GK : e / 32, mm = AK ? e / GK : e % 32;
-        const int k = k0 + kk;
-        ra[t] = (live && mm < g.M && k < g.K) ? A[mm * g.a_rs + k * g.a_cs] : 0.f;
-      }
-    }
-    if constexpr (VB) {
-#pragma unroll
-      for (int q = 0; q < N1 / 4; ++q) {
-        const int e = lane + 64 * q;
-        const int j = BK ? e / (GK / 4) : 4 * (e % 8), k = BK ? k0 + 4 * (e % (GK / 4)) : k0 + e / 8;
-        const float* src = B + k * g.b_rs + j * g.b_cs;
-        if (live && (BK ? (j < g.N && k + 3 < g.K) : (j + 3 < g.N && k < g.K))) {
-          const float4 v = *reinterpret_cast<const float4*>(src);
-          rb[4 * q] = v.x; rb[4 * q + 1] = v.y; rb[4 * q + 2] = v.z; rb[4 * q + 3] = v.w;
-        } else {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            rb[4 * q + c] = (live && (BK ? (j < g.N && k + c < g.K) : (j + c < g.N && k < g.K))) ? src[BK ? c : c * g.b_cs] : 0.f;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < N1; ++t) {
-        const int e = lane + 64 * t;
-        const int kb = BK ? e % GK : e / 32, nn = BK ? e / GK : e % 32;
-        const int kq = k0 + kb;
-        rb[t] = (live && nn < g.N && kq < g.K) ? B[kq * g.b_rs + nn * g.b_cs] : 0.f;
-      }
-    }
-  };
-  f32x16 acc = {};
-  load(0);
-  for (int k0 = 0; k0 < g.K; k0 += GK) {
-    if constexpr (VA) {
-#pragma unroll
-      for (int q = 0; q < N1 / 4; ++q) {
-        const int e = lane + 64 * q;
-        if constexpr (AK) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) As[wave][4 * (e % (GK / 4)) + c][e / (GK / 4)] = ra[4 * q + c];
-        } else {
-          *reinterpret_cast<float4*>(&As[wave][e / 8][4 * (e % 8)]) =
-              make_float4(ra[4 * q], ra[4 * q + 1], ra[4 * q + 2], ra[4 * q + 3]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < N1; ++t) {
-        const int e = lane + 64 * t;
-        As[wave][AK ? e % GK : e / 32][AK ? e / GK : e % 32] = ra[t];
-      }
-    }
-    if constexpr (VB) {
-#pragma unroll
-      for (int q = 0; q < N1 / 4; ++q) {
-        const int e = lane + 64 * q;
-        if constexpr (BK) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) Bs[wave][4 * (e % (GK / 4)) + c][e / (GK / 4)] = rb[4 * q + c];
-        } else {
-          *reinterpret_cast<float4*>(&Bs[wave][e / 8][4 * (e % 8)]) =
-              make_float4(rb[4 * q], rb[4 * q + 1], rb[4 * q + 2], rb[4 * q + 3]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < N1; ++t) {
-        const int e = lane + 64 * t;
-        Bs[wave][BK ? e % GK : e / 32][BK ? e / GK : e % 32] = rb[t];
-      }
-    }
-    __syncthreads();
-    if (k0 + GK < g.K) load(k0 + GK);
-#pragma unroll
-    for (int t = 0; t < GK / 2; ++t)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[wave][2 * t + lk][lr], Bs[wave][2 * t + lk][lr], acc, 0, 0, 0);
-    __syncthreads();
+    for (int i = 0; i < h; ++i) x[i] += x[i + h];
+  x[0] = slot_sum<32>(x[0]);                        // lanes l, l ^ 32
+  if constexpr (TS == 16) {
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[0]), __float_as_uint(x[0]), false, false);
+    x[0] = __uint_as_float(b[0]) + __uint_as_float(b[1]);
   }
-  if (!live || lr >= g.N) return;
+  return x[0];
+}
+
+template <int TS, int DH>
+struct AttnTile {
+  static constexpr int NS = 64 / TS, NA = TS * TS / 64, NQ = DH / (4 * NS), NB = DH / TS, LD = DH + 4, SIZE = TS * LD;
+  typedef float acc_t __attribute__((ext_vector_type(NA)));
+  static FE_DEV acc_t mfma(float a, float b, acc_t c) {
+    if constexpr (TS == 32) return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static FE_DEV int col() { return threadIdx.x % TS; }
+  static FE_DEV int slot() { return (threadIdx.x & 63) / TS; }
+  static FE_DEV int row(int a) { return NS * a + slot(); }                 // tile row of accumulator a
+  static FE_DEV int pos(int c) { return c / (4 * NS) * (4 * NS) + c % NS * 4 + c % (4 * NS) / NS; }   // of column c in a tile row
+  // the operands of products (s, c), c = 0..3, from one row of DH values in memory
+  static FE_DEV void row_frag(const float* p, float4 (&f)[NQ]) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = 8 * q + 4 * lk + e;
-      if (i >= g.M) continue;
-      float r = g.alpha * acc[4 * q + e];
-      const long long o = i * g.c_rs + lr;
-      if (g.bias) r += g.bias[lr];
-      if (g.R) r += Rz[o];
-      if (g.relu) r = fmaxf(r, 0.f);
-      if (g.mask && !(Mz[o] > 0.f)) r = 0.f;
-      float* c = C + o;
-      *c = g.beta != 0.f ? r + g.beta * *c : r;
+    for (int s = 0; s < NQ; ++s) {
+      const float* x = p + 4 * NS * s + slot();
+      f[s] = make_float4(x[0], x[NS], x[2 * NS], x[3 * NS]);
     }
+  }
+  // ... from row r of an LDS tile
+  static FE_DEV void tile_frag(const float* L, int r, float4 (&f)[NQ]) {
+#pragma unroll
+    for (int s = 0; s < NQ; ++s) f[s] = *reinterpret_cast<const float4*>(&L[r * LD + 4 * NS * s + 4 * slot()]);
+  }
+  // block [i][j] = rows i of the LDS tile L times the rows j held as fragments
+  static FE_DEV acc_t rows_by(const float* L, const float4 (&f)[NQ]) {
+    acc_t c = {};
+    float4 t[NQ];
+    const int i = col();
+    tile_frag(L, NS * (4 * (i / (4 * NS)) + i % 4) + i % (4 * NS) / 4, t);
+#pragma unroll
+    for (int s = 0; s < NQ; ++s) {
+      c = mfma(t[s].x, f[s].x, c);
+      c = mfma(t[s].y, f[s].y, c);
+      c = mfma(t[s].z, f[s].z, c);
+      c = mfma(t[s].w, f[s].w, c);
+    }
+    return c;
+  }
+  // out [column of L][j] += sum over the tile's rows i of L[i][.] times block [i][j]
+  static FE_DEV void cols_by(const float* L, const acc_t& p, acc_t (&out)[NB]) {
+    int at[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) at[b] = slot() * LD + pos(b * TS + col());
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) out[b] = mfma(L[NS * a * LD + at[b]], p[a], out[b]);
+  }
+  // the lane's row of DH values = out, or zeros
+  static FE_DEV void put(const acc_t (&out)[NB], float* xrow, bool ok = true) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int a = 0; a < NA; a += 4)
+        *reinterpret_cast<float4*>(xrow + b * TS + NS * a + 4 * slot()) =
+            ok ? make_float4(out[b][a], out[b][a + 1], out[b][a + 2], out[b][a + 3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+};
+
+// TS rows from row r0 of X (row stride rs, rows from n on read as zeros; n >= 1) by NT threads:
+// requested by load(), written to an LDS tile by store().
+template <int TS, int DH, int NT>
+struct AttnStage {
+  using T = AttnTile<TS, DH>;
+  static constexpr int V = TS * DH / 4 / NT, TPR = DH / 4;
+  static_assert(TS * DH % (4 * NT) == 0, "whole loads per thread");
+  float4 r[V];
+  bool ok[V];
+  static FE_DEV int row(int p) { return (threadIdx.x % NT + p * NT) / TPR; }
+  static FE_DEV int col() { return 4 * (threadIdx.x % TPR); }
+  FE_DEV void load(const float* X, long long rs, int r0, int n) {
+#pragma unroll
+    for (int p = 0; p < V; ++p) {
+      const int i = r0 + row(p);
+      ok[p] = i < n;
+      r[p] = *reinterpret_cast<const float4*>(X + min(i, n - 1) * rs + col());
+    }
+  }
+  FE_DEV void store(float* L) const {
+#pragma unroll
+    for (int p = 0; p < V; ++p) {
+      const float4 v = ok[p] ? r[p] : make_float4(0.f, 0.f, 0.f, 0.f);
+      float* d = &L[row(p) * T::LD + T::pos(col())];
+      if constexpr (TS == 32) {
+        *reinterpret_cast<float2*>(d) = make_float2(v.x, v.z);
+        *reinterpret_cast<float2*>(d + 4) = make_float2(v.y, v.w);
+      } else {
+        d[0] = v.x;
+        d[4] = v.y;
+        d[8] = v.z;
+        d[12] = v.w;
+      }
+    }
+  }
+};
+
+// Sequence, head and lengths of a (sequence, head) pair.
+struct AttnPair {
+  int z, h, nq, nk;
+  FE_DEV AttnPair(const TAttn& a, int pair) {
+    z = pair / a.H;
+    h = pair % a.H;
+    nq = a.qlen ? min(a.Sq, a.qlen[z]) : a.Sq;
+    nk = a.klen ? min(a.Sk, a.klen[z]) : a.Sk;
+  }
+};
+
+// NT > 0: keys of up to NT tiles, whose scores stay in registers between the maximum, the sum and
+// the products with the values; NT = 0: any number, the scores formed anew for each of the three.
+template <int TS, int DH, int NT, bool SMALL>
+__global__ __launch_bounds__(256, 2) void k_attn_fwd(TAttn a) {
+#pragma clang fp contract(off)
+  constexpr int NK = NT > 0 ? NT : 1;
+  using T = AttnTile<TS, DH>;
+  using St = AttnStage<TS, DH, SMALL ? 64 : 256>;
+  static_assert(!SMALL || NT == 1, "a wave per sequence holds one tile");
+  constexpr int NBUF = SMALL ? 8 : 2;               // two tiles (K, V) per wave, or two buffers of the workgroup
+  __shared__ __align__(16) float Xs[NBUF][T::SIZE];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int id = xcd_tile(blockIdx.x, gridDim.x);
+  const int groups = SMALL ? 1 : (a.Sq + 4 * TS - 1) / (4 * TS);
+  const int pair = SMALL ? 4 * id + wave : id / groups;
+  if (SMALL && pair >= a.nseq * a.H) return;        // waves share nothing
+  const AttnPair P(a, pair);
+  const int q = (SMALL ? 0 : (id % groups * 4 + wave) * TS) + T::col();
+  const float* K = a.k + P.z * a.k_bs + P.h * DH;
+  const float* Vv = a.v + P.z * a.v_bs + P.h * DH;
+  float4 qf[T::NQ];
+  T::row_frag(a.q + P.z * a.q_bs + P.h * DH + min(q, a.Sq - 1) * a.q_rs, qf);
+  St st;
+  int cur = SMALL ? 2 * wave : 0;
+  // The next staged tile, and the request for the one after it (null: none).  Storing to a buffer
+  // follows every read of it: those precede the last barrier but one of the wave that read.
+  auto next = [&](const float* X, long long rs, int r0) -> const float* {
+    const float* tile = Xs[cur];
+    st.store(Xs[cur]);
+    if constexpr (SMALL) wave_sync();
+    else lds_barrier();
+    if (X) st.load(X, rs, r0, P.nk);
+    cur ^= 1;
+    return tile;
+  };
+  float m = -INFINITY, inv = 0.f;
+  typename T::acc_t s[NK], o[T::NB] = {};
+  if (P.nk > 0) st.load(K, a.k_rs, 0, P.nk);        // with no key at all every loop below is empty
+  if constexpr (NT > 0) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (t * TS >= P.nk) {
+        s[t] = typename T::acc_t{};
+        continue;
+      }
+      const bool last = (t + 1) * TS >= P.nk;
+      const float* tile = last ? next(Vv, a.v_rs, 0) : next(K, a.k_rs, (t + 1) * TS);
+      s[t] = T::rows_by(tile, qf);
+#pragma unroll
+      for (int i = 0; i < T::NA; ++i) {
+        s[t][i] = t * TS + T::row(i) < P.nk ? s[t][i] * a.scale : -INFINITY;
+        m = fmaxf(m, s[t][i]);
+      }
+    }
+    m = slot_max<TS>(m);
+    typename T::acc_t part[2] = {};
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t * TS < P.nk)
+#pragma unroll
+        for (int i = 0; i < T::NA; ++i) {
+          s[t][i] = expf(s[t][i] - m);
+          part[t & 1][i] += s[t][i];
+        }
+    inv = 1.f / tree_sum<TS>(part[0], part[1]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t * TS < P.nk) {
+        const bool more = (t + 1) * TS < P.nk;
+        const float* tile = next(more ? Vv : nullptr, a.v_rs, (t + 1) * TS);
+#pragma unroll
+        for (int i = 0; i < T::NA; ++i) s[t][i] *= inv;
+        T::cols_by(tile, s[t], o);
+      }
+  } else {
+    const bool fused = a.Sk > 512;                  // exp's argument with one rounding
+    for (int k0 = 0; k0 < P.nk; k0 += TS) {
+      const bool more = k0 + TS < P.nk;
+      const float* tile = next(K, a.k_rs, more ? k0 + TS : 0);
+      s[0] = T::rows_by(tile, qf);
+#pragma unroll
+      for (int i = 0; i < T::NA; ++i)
+        if (k0 + T::row(i) < P.nk) m = fmaxf(m, s[0][i] * a.scale);
+    }
+    m = slot_max<TS>(m);
+    auto probs = [&](const float* tile, int k0) {
+      s[0] = T::rows_by(tile, qf);
+#pragma unroll
+      for (int i = 0; i < T::NA; ++i) {
+        const float x = fused ? fmaf(s[0][i], a.scale, -m) : s[0][i] * a.scale - m;
+        s[0][i] = k0 + T::row(i) < P.nk ? expf(x) : 0.f;
+      }
+    };
+    typename T::acc_t part[2] = {};
+    for (int k0 = 0; k0 < P.nk; k0 += TS) {
+      const bool more = k0 + TS < P.nk;
+      probs(next(K, a.k_rs, more ? k0 + TS : 0), k0);
+      if ((k0 / TS) & 1) part[1] += s[0];
+      else part[0] += s[0];
+    }
+    inv = 1.f / tree_sum<TS>(part[0], part[1]);
+    for (int k0 = 0; k0 < P.nk; k0 += TS) {
+      const bool more = k0 + TS < P.nk;
+      probs(next(Vv, a.v_rs, k0), k0);
+#pragma unroll
+      for (int i = 0; i < T::NA; ++i) s[0][i] *= inv;
+      T::cols_by(next(more ? K : nullptr, a.k_rs, k0 + TS), s[0], o);
+    }
+  }
+  if (q >= a.Sq) return;
+  const bool ok = q < P.nq && P.nk > 0;             // other queries attend to nothing: zero rows
+  T::put(o, a.o + P.z * a.o_bs + P.h * DH + q * a.o_rs, ok);
+  if (T::slot() == 0) a.stat[((long long)P.z * a.H + P.h) * a.Sq + q] = ok ? make_float2(m, inv) : make_float2(INFINITY, 0.f);
+}
+
+// dK and dV of the wave's TS keys (fragments kf, vf; kok: this lane's key exists) from one tile of
+// queries Qt, output gradients Ot, and their statistics and D = rowsum(dO O).
+template <int TS, int DH>
+FE_DEV void attn_kv_tile(const float* Qt, const float* Ot, const float2* stat, const float* Dr, float scale, bool kok,
+                         const float4 (&kf)[AttnTile<TS, DH>::NQ], const float4 (&vf)[AttnTile<TS, DH>::NQ],
+                         typename AttnTile<TS, DH>::acc_t (&dk)[AttnTile<TS, DH>::NB],
+                         typename AttnTile<TS, DH>::acc_t (&dv)[AttnTile<TS, DH>::NB]) {
+  using T = AttnTile<TS, DH>;
+  typename T::acc_t p = T::rows_by(Qt, kf), ds = T::rows_by(Ot, vf);
+#pragma unroll
+  for (int i = 0; i < T::NA; ++i) {
+    const float2 st = stat[T::row(i)];
+    p[i] = kok ? expf(p[i] * scale - st.x) * st.y : 0.f;
+    ds[i] = scale * p[i] * (ds[i] - Dr[T::row(i)]);
+  }
+  T::cols_by(Ot, p, dv);
+  T::cols_by(Qt, ds, dk);
+}
+
+// dQ of the wave's TS queries (fragments qf, of; their statistics and D) from one tile of keys and values
+// whose first `nk` rows exist.
+template <int TS, int DH>
+FE_DEV void attn_q_tile(const float* Kt, const float* Vt, float2 st, float D, float scale, int nk,
+                        const float4 (&qf)[AttnTile<TS, DH>::NQ], const float4 (&of)[AttnTile<TS, DH>::NQ],
+                        typename AttnTile<TS, DH>::acc_t (&dq)[AttnTile<TS, DH>::NB]) {
+  using T = AttnTile<TS, DH>;
+  typename T::acc_t p = T::rows_by(Kt, qf), ds = T::rows_by(Vt, of);
+#pragma unroll
+  for (int i = 0; i < T::NA; ++i) ds[i] = T::row(i) < nk ? scale * (expf(p[i] * scale - st.x) * st.y) * (ds[i] - D) : 0.f;
+  T::cols_by(Kt, ds, dq);
+}
+
+template <int TS, int DH>
+FE_DEV float attn_dot(const float4 (&x)[AttnTile<TS, DH>::NQ], const float4 (&y)[AttnTile<TS, DH>::NQ]) {
+  float t = 0.f;
+#pragma unroll
+  for (int s = 0; s < AttnTile<TS, DH>::NQ; ++s)
+    t += x[s].x * y[s].x + x[s].y * y[s].y + x[s].z * y[s].z + x[s].w * y[s].w;
+  return slot_sum<TS>(t);
+}
+
+// Long sequences: workgroups 0 .. n_kv - 1 (after the XCD order) form dK and dV of 4 TS keys each, the
+// others dQ of 4 TS queries each.
+template <int TS, int DH>
+__global__ __launch_bounds__(256, DH == 32 ? 3 : 2) void k_attn_bwd(TAttn a, int n_kv) {
+  using T = AttnTile<TS, DH>;
+  using St = AttnStage<TS, DH, 256>;
+  __shared__ __align__(16) float Xs[2][T::SIZE];
+  __shared__ __align__(16) float Ys[2][T::SIZE];
+  __shared__ __align__(16) float2 s_stat[2][TS];
+  __shared__ __align__(16) float s_D[2][TS];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool is_kv = (int)blockIdx.x < n_kv;
+  const int id = is_kv ? xcd_tile(blockIdx.x, n_kv) : xcd_tile(blockIdx.x - n_kv, gridDim.x - n_kv);
+  const int groups = ((is_kv ? a.Sk : a.Sq) + 4 * TS - 1) / (4 * TS);
+  const AttnPair P(a, id / groups);
+  const int own = (id % groups * 4 + wave) * TS + T::col();   // this lane's key or query
+  const float* Q = a.q + P.z * a.q_bs + P.h * DH;
+  const float* K = a.k + P.z * a.k_bs + P.h * DH;
+  const float* Vv = a.v + P.z * a.v_bs + P.h * DH;
+  const float* O = a.o + P.z * a.o_bs + P.h * DH;
+  const float* dO = a.dO + P.z * a.do_bs + P.h * DH;
+  const float2* stat = a.stat + ((long long)P.z * a.H + P.h) * a.Sq;
+  int cur = 0;
+  if (is_kv) {
+    float4 kf[T::NQ], vf[T::NQ];
+    T::row_frag(K + min(own, a.Sk - 1) * a.k_rs, kf);
+    T::row_frag(Vv + min(own, a.Sk - 1) * a.v_rs, vf);
+    typename T::acc_t dk[T::NB] = {}, dv[T::NB] = {};
+    St sq, sdo, so;
+    float2 st = make_float2(INFINITY, 0.f);
+    auto load = [&](int q0) {
+      sq.load(Q, a.q_rs, q0, P.nq);
+      sdo.load(dO, a.do_rs, q0, P.nq);
+      so.load(O, a.o_rs, q0, P.nq);
+      if (threadIdx.x < TS) st = q0 + (int)threadIdx.x < P.nq ? stat[q0 + threadIdx.x] : make_float2(INFINITY, 0.f);
+    };
+    const int nq = P.nk > 0 ? P.nq : 0;
+    if (nq > 0) load(0);
+    for (int q0 = 0; q0 < nq; q0 += TS, cur ^= 1) {
+      sq.store(Xs[cur]);
+      sdo.store(Ys[cur]);
+#pragma unroll
+      for (int p = 0; p < St::V; ++p) {             // D of the tile's rows: TPR neighbouring lanes hold one
+        const float4 x = sdo.r[p], y = so.r[p];
+        float t = x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
+#pragma unroll
+        for (int s = St::TPR / 2; s > 0; s >>= 1) t += __shfl_xor(t, s, 64);
+        if (threadIdx.x % St::TPR == 0) s_D[cur][St::row(p)] = sdo.ok[p] ? t : 0.f;
+      }
+      if (threadIdx.x < TS) s_stat[cur][threadIdx.x] = st;
+      lds_barrier();
+      if (q0 + TS < nq) load(q0 + TS);
+      attn_kv_tile<TS, DH>(Xs[cur], Ys[cur], s_stat[cur], s_D[cur], a.scale, own < P.nk, kf, vf, dk, dv);
+    }
+    if (own >= a.Sk) return;
+    T::put(dk, a.dk + P.z * a.k_bs + P.h * DH + own * a.k_rs);
+    T::put(dv, a.dv + P.z * a.v_bs + P.h * DH + own * a.v_rs);
+    return;
+  }
+  float4 qf[T::NQ], of[T::NQ], oo[T::NQ];
+  const int qc = min(own, a.Sq - 1);
+  T::row_frag(Q + qc * a.q_rs, qf);
+  T::row_frag(dO + qc * a.do_rs, of);
+  T::row_frag(O + qc * a.o_rs, oo);
+  const float2 st = stat[qc];
+  St sk, sv;
+  if (P.nk > 0) {
+    sk.load(K, a.k_rs, 0, P.nk);
+    sv.load(Vv, a.v_rs, 0, P.nk);
+  }
+  const float D = attn_dot<TS, DH>(of, oo);
+  typename T::acc_t dq[T::NB] = {};
+  for (int k0 = 0; k0 < P.nk; k0 += TS, cur ^= 1) {
+    sk.store(Xs[cur]);
+    sv.store(Ys[cur]);
+    lds_barrier();
+    if (k0 + TS < P.nk) {
+      sk.load(K, a.k_rs, k0 + TS, P.nk);
+      sv.load(Vv, a.v_rs, k0 + TS, P.nk);
+    }
+    attn_q_tile<TS, DH>(Xs[cur], Ys[cur], st, D, a.scale, P.nk - k0, qf, of, dq);
+  }
+  if (own < a.Sq) T::put(dq, a.dq + P.z * a.q_bs + P.h * DH + own * a.q_rs);
+}
+
+// Sequences of at most TS queries and keys: a wave per (sequence, head), all three gradients.
+template <int TS, int DH>
+__global__ __launch_bounds__(128) void k_attn_bwd_small(TAttn a) {
+  using T = AttnTile<TS, DH>;
+  using St = AttnStage<TS, DH, 64>;
+  __shared__ __align__(16) float Qs[2][T::SIZE], Os[2][T::SIZE], Ks[2][T::SIZE], Vs[2][T::SIZE];
+  __shared__ __align__(16) float2 s_stat[2][TS];
+  __shared__ __align__(16) float s_D[2][TS];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pair = 2 * xcd_tile(blockIdx.x, gridDim.x) + wave;
+  if (pair >= a.nseq * a.H) return;                 // waves share nothing
+  const AttnPair P(a, pair);
+  const int c = T::col();
+  const float* O = a.o + P.z * a.o_bs + P.h * DH;
+  float* dqp = a.dq + P.z * a.q_bs + P.h * DH + c * a.q_rs;
+  float* dkp = a.dk + P.z * a.k_bs + P.h * DH + c * a.k_rs;
+  float* dvp = a.dv + P.z * a.v_bs + P.h * DH + c * a.v_rs;
+  typename T::acc_t dq[T::NB] = {}, dk[T::NB] = {}, dv[T::NB] = {};
+  if (P.nq > 0 && P.nk > 0) {
+    St sq, so, sk, sv;
+    float4 of[T::NQ], oo[T::NQ], f0[T::NQ], f1[T::NQ];
+    sq.load(a.q + P.z * a.q_bs + P.h * DH, a.q_rs, 0, P.nq);
+    so.load(a.dO + P.z * a.do_bs + P.h * DH, a.do_rs, 0, P.nq);
+    sk.load(a.k + P.z * a.k_bs + P.h * DH, a.k_rs, 0, P.nk);
+    sv.load(a.v + P.z * a.v_bs + P.h * DH, a.v_rs, 0, P.nk);
+    T::row_frag(O + min(c, P.nq - 1) * a.o_rs, oo);
+    const float2 st = c < P.nq ? a.stat[((long long)P.z * a.H + P.h) * a.Sq + c] : make_float2(INFINITY, 0.f);
+    sq.store(Qs[wave]);
+    so.store(Os[wave]);
+    sk.store(Ks[wave]);
+    sv.store(Vs[wave]);
+    wave_sync();
+    T::tile_frag(Os[wave], c, of);
+    const float D = attn_dot<TS, DH>(of, oo);
+    if (T::slot() == 0) {
+      s_stat[wave][c] = st;
+      s_D[wave][c] = D;
+    }
+    wave_sync();
+    T::tile_frag(Ks[wave], c, f0);
+    T::tile_frag(Vs[wave], c, f1);
+    attn_kv_tile<TS, DH>(Qs[wave], Os[wave], s_stat[wave], s_D[wave], a.scale, c < P.nk, f0, f1, dk, dv);
+    T::tile_frag(Qs[wave], c, f0);
+    attn_q_tile<TS, DH>(Ks[wave], Vs[wave], st, D, a.scale, P.nk, f0, of, dq);
+  }
+  if (c < a.Sq) T::put(dq, dqp);
+  if (c < a.Sk) {
+    T::put(dk, dkp);
+    T::put(dv, dvp);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -481,91 +821,6 @@ __global__ __launch_bounds__(256) void k_ln_bwd_params(const float* X, long long
   if (w == 0 && j < d) {
     atomicAdd(&dg[j], part[0][0][c] + part[0][1][c] + part[0][2][c] + part[0][3][c]);
     atomicAdd(&db[j], part[1][0][c] + part[1][1][c] + part[1][2][c] + part[1][3][c]);
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// Softmax over the keys of every score row: P = softmax(scale S) on keys j < klen(z1), 0 beyond;
-// query rows i >= qlen(z1) are all zero.  Row r of batch z = z1*nb2 + z2 is S + z*nq*nk + r*nk.
-// ------------------------------------------------------------------------------------------
-// One wave per row; NV > 0: the row (nk <= 64 NV) stays in registers between the passes, NV = 0: it
-// is re-read from memory (longer rows).
-template <int NV>
-__global__ __launch_bounds__(256) void k_softmax_fwd(const float* S, float* P, int nbatch, int nb2, int nq, int nk,
-                                                     float scale, const int32_t* qlen, const int32_t* klen) {
-  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= (long long)nbatch * nq) return;
-  const int z = (int)(row / nq), i = (int)(row % nq), z1 = z / nb2;
-  const int kl = klen ? min(nk, klen[z1]) : nk;
-  const bool live = (qlen ? i < qlen[z1] : true) && kl > 0;
-  const float* s = S + row * nk;
-  float* p = P + row * nk;
-  if constexpr (NV > 0) {
-    float v[NV];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int j = lane + 64 * u;
-      v[u] = j < kl ? s[j] * scale : -INFINITY;
-      mx = fmaxf(mx, v[u]);
-    }
-    mx = wave_max(mx);
-    float sum = 0.f;
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int j = lane + 64 * u;
-      v[u] = j < kl ? expf(v[u] - mx) : 0.f;
-      sum += v[u];
-    }
-    sum = wave_sum(sum);
-    const float inv = live ? 1.f / sum : 0.f;
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int j = lane + 64 * u;
-      if (j < nk) p[j] = v[u] * inv;
-    }
-  } else {
-    float mx = -INFINITY;
-    for (int j = lane; j < kl; j += 64) mx = fmaxf(mx, s[j] * scale);
-    mx = wave_max(mx);
-    float sum = 0.f;
-    for (int j = lane; j < kl; j += 64) sum += expf(s[j] * scale - mx);
-    sum = wave_sum(sum);
-    const float inv = live ? 1.f / sum : 0.f;
-    for (int j = lane; j < nk; j += 64) p[j] = (live && j < kl) ? expf(s[j] * scale - mx) * inv : 0.f;
-  }
-}
-
-// dS = scale P (dP - sum_j P_j dP_j), in place over dP.
-template <int NV>
-__global__ __launch_bounds__(256) void k_softmax_bwd(const float* P, float* dP, long long rows, int nk, float scale) {
-  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= rows) return;
-  const float* p = P + row * nk;
-  float* dp = dP + row * nk;
-  if constexpr (NV > 0) {
-    float pv[NV], gv[NV];
-    float s = 0.f;
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int j = lane + 64 * u;
-      pv[u] = j < nk ? p[j] : 0.f;
-      gv[u] = j < nk ? dp[j] : 0.f;
-      s += pv[u] * gv[u];
-    }
-    s = wave_sum(s);
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int j = lane + 64 * u;
-      if (j < nk) dp[j] = scale * pv[u] * (gv[u] - s);
-    }
-  } else {
-    float s = 0.f;
-    for (int j = lane; j < nk; j += 64) s += p[j] * dp[j];
-    s = wave_sum(s);
-    for (int j = lane; j < nk; j += 64) dp[j] = scale * p[j] * (dp[j] - s);
   }
 }
 
@@ -735,77 +990,52 @@ inline unsigned blocks(long long n) { return (unsigned)((n + 255) / 256); }
 }  // namespace
 
 template <int WM, int WN, bool AK, bool BK, bool VA, bool VB>
-void gemm_launch(const TGemm& g, long long total, hipStream_t s) {
+void gemm_launch(const TGemm& g, int chunks, hipStream_t s) {
   constexpr int TM = 32 * WM, TN = 32 * WN;
   const int tiles_n = (g.N + TN - 1) / TN, tiles = tiles_n * ((g.M + TM - 1) / TM);
-  const long long per = std::max(1LL, (1LL << 22) / tiles);   // batch items or k chunks per launch
-  for (long long z0 = 0; z0 < total; z0 += per)
-    hipLaunchKernelGGL((k_gemm<WM, WN, AK, BK, VA, VB>), dim3((unsigned)(std::min(per, total - z0) * tiles)), dim3(256), 0, s, g,
-                       (int)z0, g.nbatch, tiles_n, tiles);
+  const int per = std::max(1, (1 << 22) / tiles);   // k chunks per launch
+  for (int c = 0; c < chunks; c += per)
+    hipLaunchKernelGGL((k_gemm<WM, WN, AK, BK, VA, VB>), dim3((unsigned)(std::min(per, chunks - c) * tiles)), dim3(256), 0, s, g,
+                       c, tiles_n, tiles);
 }
 
 // float4 loads of an operand are possible when its base and every stride but the contiguous one
 // are multiples of four floats (so every group of four along the contiguous index is aligned) and so
 // is the extent of the contiguous index (so no group is cut)
-inline bool vec4(const float* p, long long other_stride, long long b1, long long b2, int extent) {
-  return reinterpret_cast<uintptr_t>(p) % 16 == 0 && other_stride % 4 == 0 && b1 % 4 == 0 && b2 % 4 == 0 && extent % 4 == 0;
+inline bool vec4(const float* p, long long other_stride, int extent) {
+  return reinterpret_cast<uintptr_t>(p) % 16 == 0 && other_stride % 4 == 0 && extent % 4 == 0;
 }
 
 template <int WM, int WN, bool AK, bool BK>
-void gemm_vec(const TGemm& g, long long total, hipStream_t s) {
-  const bool va = vec4(g.A, AK ? g.a_rs : g.a_cs, g.a_b1, g.a_b2, AK ? g.K : g.M) && (AK ? g.a_cs == 1 : g.a_rs == 1);
-  const bool vb = vec4(g.B, BK ? g.b_cs : g.b_rs, g.b_b1, g.b_b2, BK ? g.K : g.N) && (BK ? g.b_rs == 1 : g.b_cs == 1);
-  if (va && vb) gemm_launch<WM, WN, AK, BK, true, true>(g, total, s);
-  else if (va) gemm_launch<WM, WN, AK, BK, true, false>(g, total, s);
-  else if (vb) gemm_launch<WM, WN, AK, BK, false, true>(g, total, s);
-  else gemm_launch<WM, WN, AK, BK, false, false>(g, total, s);
+void gemm_vec(const TGemm& g, int chunks, hipStream_t s) {
+  const bool va = vec4(g.A, AK ? g.a_rs : g.a_cs, AK ? g.K : g.M) && (AK ? g.a_cs == 1 : g.a_rs == 1);
+  const bool vb = vec4(g.B, BK ? g.b_cs : g.b_rs, BK ? g.K : g.N) && (BK ? g.b_rs == 1 : g.b_cs == 1);
+  if (va && vb) gemm_launch<WM, WN, AK, BK, true, true>(g, chunks, s);
+  else if (va) gemm_launch<WM, WN, AK, BK, true, false>(g, chunks, s);
+  else if (vb) gemm_launch<WM, WN, AK, BK, false, true>(g, chunks, s);
+  else gemm_launch<WM, WN, AK, BK, false, false>(g, chunks, s);
 }
 
 template <int WM, int WN>
-void gemm_orient(const TGemm& g, long long total, hipStream_t s) {
+void gemm_orient(const TGemm& g, int chunks, hipStream_t s) {
   const bool ak = g.a_cs == 1 && g.a_rs != 1, bk = g.b_rs == 1 && g.b_cs != 1;
-  if (ak && bk) gemm_vec<WM, WN, true, true>(g, total, s);
-  else if (ak) gemm_vec<WM, WN, true, false>(g, total, s);
-  else if (bk) gemm_vec<WM, WN, false, true>(g, total, s);
-  else gemm_vec<WM, WN, false, false>(g, total, s);
-}
-
-template <bool AK, bool BK>
-void small_launch_vec(bool va, bool vb, const TGemm& g, unsigned nblk, int z0, hipStream_t s) {
-  if (va && vb) hipLaunchKernelGGL((k_gemm_small<AK, BK, true, true>), dim3(nblk), dim3(256), 0, s, g, z0);
-  else if (va) hipLaunchKernelGGL((k_gemm_small<AK, BK, true, false>), dim3(nblk), dim3(256), 0, s, g, z0);
-  else if (vb) hipLaunchKernelGGL((k_gemm_small<AK, BK, false, true>), dim3(nblk), dim3(256), 0, s, g, z0);
-  else hipLaunchKernelGGL((k_gemm_small<AK, BK, false, false>), dim3(nblk), dim3(256), 0, s, g, z0);
-}
-
-void small_launch(bool ak, bool bk, bool va, bool vb, const TGemm& g, unsigned nblk, int z0, hipStream_t s) {
-  if (ak && bk) small_launch_vec<true, true>(va, vb, g, nblk, z0, s);
-  else if (ak) small_launch_vec<true, false>(va, vb, g, nblk, z0, s);
-  else if (bk) small_launch_vec<false, true>(va, vb, g, nblk, z0, s);
-  else small_launch_vec<false, false>(va, vb, g, nblk, z0, s);
+  if (ak && bk) gemm_vec<WM, WN, true, true>(g, chunks, s);
+  else if (ak) gemm_vec<WM, WN, true, false>(g, chunks, s);
+  else if (bk) gemm_vec<WM, WN, false, true>(g, chunks, s);
+  else gemm_vec<WM, WN, false, false>(g, chunks, s);
 }
 
 hipError_t t_gemm(const TGemm& g, hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0 || g.nbatch <= 0) return hipSuccess;
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.ksplit > 0 && (g.beta != 1.f || g.bias || g.R || g.relu || g.mask || g.ksplit % GK)) return hipErrorInvalidValue;
-  if (g.colsum && g.nbatch != 1) return hipErrorInvalidValue;
   // a tile's byte offsets are 32-bit (at most 128 rows and 32 k values of either operand)
   for (long long st : {g.a_rs, g.a_cs, g.b_rs, g.b_cs})
     if (st < 0 || st > (1 << 21)) return hipErrorInvalidValue;
-  const int nk = g.ksplit > 0 ? (g.K + g.ksplit - 1) / g.ksplit : 1;
-  const long long total = (long long)g.nbatch * nk;
-  if (g.M <= 32 && g.N <= 32 && g.ksplit == 0 && !g.colsum) {
-    const bool ak = g.a_cs == 1 && g.a_rs != 1, bk = g.b_rs == 1 && g.b_cs != 1;
-    const bool va = vec4(g.A, ak ? g.a_rs : g.a_cs, g.a_b1, g.a_b2, ak ? g.K : g.M) && (ak ? g.a_cs == 1 : g.a_rs == 1);
-    const bool vb = vec4(g.B, bk ? g.b_cs : g.b_rs, g.b_b1, g.b_b2, bk ? g.K : g.N) && (bk ? g.b_rs == 1 : g.b_cs == 1);
-    for (long long z0 = 0; z0 < total; z0 += 4LL * 65535) {
-      const unsigned nblk = (unsigned)std::min<long long>(65535, (total - z0 + 3) / 4);
-      small_launch(ak, bk, va, vb, g, nblk, (int)z0, s);
-    }
-  } else if (g.N <= 32) {
-    gemm_orient<4, 1>(g, total, s);                 // 128 x 32 tiles (one head's width)
+  const int chunks = g.ksplit > 0 ? (g.K + g.ksplit - 1) / g.ksplit : 1;
+  if (g.N <= 32) {
+    gemm_orient<4, 1>(g, chunks, s);                 // 128 x 32 tiles (the head)
   } else {
-    gemm_orient<2, 2>(g, total, s);                 // 64 x 64 tiles
+    gemm_orient<2, 2>(g, chunks, s);                 // 64 x 64 tiles
   }
   return hipGetLastError();
 }
@@ -848,34 +1078,52 @@ hipError_t t_ln_bwd(const float* X, long long x_rs, int rows, int d, const float
   return hipGetLastError();
 }
 
-template <class F>
-void by_row_length(int nk, F&& launch) {
-  if (nk <= 64) launch(std::integral_constant<int, 1>());
-  else if (nk <= 128) launch(std::integral_constant<int, 2>());
-  else if (nk <= 256) launch(std::integral_constant<int, 4>());
-  else if (nk <= 512) launch(std::integral_constant<int, 8>());
-  else launch(std::integral_constant<int, 0>());
+template <int DH>
+hipError_t attn_fwd_dh(const TAttn& a, hipStream_t s) {
+  const long long pairs = (long long)a.nseq * a.H;
+  const dim3 grid((unsigned)(pairs * ((a.Sq + 127) / 128)));
+  const dim3 small((unsigned)((pairs + 3) / 4));
+  const int most = std::max(a.Sq, a.Sk);
+  if (most <= 16) hipLaunchKernelGGL((k_attn_fwd<16, DH, 1, true>), small, dim3(256), 0, s, a);
+  else if (most <= 32) hipLaunchKernelGGL((k_attn_fwd<32, DH, 1, true>), small, dim3(256), 0, s, a);
+  else if (a.Sk <= 256) hipLaunchKernelGGL((k_attn_fwd<32, DH, 8, false>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_attn_fwd<32, DH, 0, false>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
 }
-
-hipError_t t_softmax_fwd(const float* S, float* P, int nbatch, int nb2, int nq, int nk, float scale,
-                         const int32_t* qlen, const int32_t* klen, hipStream_t s) {
-  const long long rows = (long long)nbatch * nq;
-  if (rows <= 0) return hipSuccess;
-  by_row_length(nk, [&](auto nv) {
-    hipLaunchKernelGGL((k_softmax_fwd<decltype(nv)::value>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, S, P,
-                       nbatch, nb2, nq, nk, scale, qlen, klen);
-  });
+template <int DH>
+hipError_t attn_bwd_dh(const TAttn& a, hipStream_t s) {
+  const int most = std::max(a.Sq, a.Sk);
+  const long long pairs = (long long)a.nseq * a.H;
+  const dim3 small((unsigned)((pairs + 1) / 2));
+  if (most <= 16) {
+    hipLaunchKernelGGL((k_attn_bwd_small<16, DH>), small, dim3(128), 0, s, a);
+  } else if (most <= 32) {
+    hipLaunchKernelGGL((k_attn_bwd_small<32, DH>), small, dim3(128), 0, s, a);
+  } else {
+    const int n_kv = (int)(pairs * ((a.Sk + 127) / 128));
+    hipLaunchKernelGGL((k_attn_bwd<32, DH>), dim3((unsigned)(n_kv + pairs * ((a.Sq + 127) / 128))), dim3(256), 0, s, a, n_kv);
+  }
   return hipGetLastError();
 }
 
-hipError_t t_softmax_bwd(const float* P, float* dP, long long rows, int nk, float scale, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  by_row_length(nk, [&](auto nv) {
-    hipLaunchKernelGGL((k_softmax_bwd<decltype(nv)::value>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, P, dP,
-                       rows, nk, scale);
-  });
-  return hipGetLastError();
+// every row of every head at a 16-byte boundary
+inline bool attn_ok(const TAttn& a) {
+  for (long long st : {a.q_rs, a.k_rs, a.v_rs, a.o_rs, a.q_bs, a.k_bs, a.v_bs, a.o_bs})
+    if (st % 4) return false;
+  return (a.dh == 32 || a.dh == 64) && a.Sq > 0 && a.Sk > 0;
 }
+
+hipError_t t_attn_fwd(const TAttn& a, hipStream_t s) {
+  if (a.nseq <= 0) return hipSuccess;
+  if (!attn_ok(a)) return hipErrorInvalidValue;
+  return a.dh == 32 ? attn_fwd_dh<32>(a, s) : attn_fwd_dh<64>(a, s);
+}
+hipError_t t_attn_bwd(const TAttn& a, hipStream_t s) {
+  if (a.nseq <= 0) return hipSuccess;
+  if (!attn_ok(a) || a.do_rs % 4 || a.do_bs % 4) return hipErrorInvalidValue;
+  return a.dh == 32 ? attn_bwd_dh<32>(a, s) : attn_bwd_dh<64>(a, s);
+}
+
 hipError_t t_copy(const float* x, float* y, long long n, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(k_copy, dim3(blocks(n)), dim3(256), 0, s, x, y, n);
   return hipGetLastError();

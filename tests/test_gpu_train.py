@@ -225,3 +225,18 @@ def test_product_edges(d, heads, B, T, K, L, M):
     c = gen.config(1, B=B, T=T, K=K, L=L, M=M, d=d, n_heads=heads, ffn=4 * d, n_layers=1, dtype="f32")
     W, I = gen.make_weights(c), gen.make_inputs(c)
     check(c, W, I, _relevance(c), "mse")
+
+
+@pytest.mark.parametrize("d, heads, B, T, K, L, M", [
+    (32, 1, 3, 16, 17, 15, 20),      # one 16-row tile; 17 lists: one row past it
+    (64, 2, 2, 32, 33, 31, 40),      # one 32-row tile for a wave; 33 lists: the tiled form's shortest
+    (64, 1, 2, 17, 5, 16, 33),       # head width 64, 17 rows: 32-row tile of a wave
+    (32, 1, 1, 256, 130, 2, 129),    # the last length whose scores stay in registers; one row past 128
+    (64, 1, 1, 257, 3, 4, 12),       # the first length whose scores are formed anew, head width 64
+    (32, 1, 1, 545, 3, 4, 12),       # past 512 keys, 33 rows in the last workgroup
+])
+def test_attention_edges(d, heads, B, T, K, L, M):
+    """Edges of the attention kernels' tiles and forms, forward (scores) and backward."""
+    c = gen.config(1, B=B, T=T, K=K, L=L, M=M, d=d, n_heads=heads, ffn=2 * d, n_layers=1, dtype="f32")
+    W, I = gen.make_weights(c), gen.make_inputs(c)
+    check(c, W, I, _relevance(c), "bce")
