@@ -70,15 +70,42 @@ FE_DEV bool block_any(int pred) {
   return r != 0;
 }
 
+// Value of another lane of the same 16-lane row, by a DPP control word (row_ror:n is 0x120 + n,
+// quad_perm:[a,b,c,d] is a | b << 2 | c << 4 | d << 6): VALU, no LDS round trip.
+template <int CTRL>
+FE_DEV float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// Butterflies over all 64 lanes: xor 32, 16 (lane swaps), 8, 4 (rotations of a row: after the
+// step before, values repeat every 16, then 8 lanes, so lane + 8 and lane + 4 stand for lane ^ 8
+// and lane ^ 4), 2, 1 (quad permutes).  Same pairs in the same order as a chain of xor shuffles
+// (which go through LDS, ~100 cycles each), so sums have the same bits.
 FE_DEV float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  v += dpp<0x128>(v);
+  v += dpp<0x124>(v);
+  v += dpp<0x4e>(v);
+  return v + dpp<0xb1>(v);
 }
 FE_DEV float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  v = rows_max(v);
+  v = fmaxf(v, dpp<0x128>(v));
+  v = fmaxf(v, dpp<0x124>(v));
+  v = fmaxf(v, dpp<0x4e>(v));
+  return fmaxf(v, dpp<0xb1>(v));
+}
+// ... over the 32 lanes of a wave half.
+FE_DEV float half_sum(float v) {
+  auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  v += dpp<0x128>(v);
+  v += dpp<0x124>(v);
+  v += dpp<0x4e>(v);
+  return v + dpp<0xb1>(v);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -18,13 +18,6 @@ FE_DEV void load4(const void* p, bool f32, float* v) {
   }
 }
 
-// Sum over the 32 lanes of a wave half.
-FE_DEV float half_sum(float v) {
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // A workgroup of four waves owns GM x GN outputs, each wave 16 rows by two 16 x 16 blocks; k is
 // staged through LDS in steps of up to GKC.  fp32 models answer small requests (a launch has one to
 // a few tiles, K = d or 4d), so a launch is its chain of memory round trips: a step loads its whole

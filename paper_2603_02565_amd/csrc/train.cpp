@@ -340,14 +340,14 @@ hipError_t enc_bwd(const float* W, float* G, const EncP& p, const EncAct& a, con
   TRY(linear_dx(dx, d, R, d, W + p.w2, F, pl.tF, F, false, a.a1, s));
   TRY(linear_dw(a.h2, d, R, d, pl.tF, F, F, G + p.w1, G + p.b1, s));
   TRY(linear_dx(pl.tF, F, R, F, W + p.w1, d, pl.td, d, false, nullptr, s));
-  TRY(t_ln_bwd(a.x2, d, R, d, W + p.ln2g, a.m2, a.r2, pl.td, d, dx, d, G + p.ln2g, G + p.ln2b, s));
+  TRY(t_ln_bwd(a.x2, d, R, d, W + p.ln2g, a.m2, a.r2, pl.td, d, dx, d, true, G + p.ln2g, G + p.ln2b, s));
   // self-attention
   TRY(linear_dw(a.o, d, R, d, dx, d, d, G + p.wo, G + p.bo, s));
   TRY(linear_dx(dx, d, R, d, W + p.wo, d, pl.td, d, false, nullptr, s));
   TRY(t_attn_bwd(self_attn_bwd(self_attn(a.qkv, D, nseq, S, valid, a.st, a.o), D, pl.td, pl.dqkv), s));
   TRY(linear_dw(a.h1, d, R, d, pl.dqkv, 3 * d, 3 * d, G + p.wqkv, G + p.bqkv, s));
   TRY(linear_dx(pl.dqkv, 3 * d, R, 3 * d, W + p.wqkv, d, pl.td, d, false, nullptr, s));
-  return t_ln_bwd(a.x, d, R, d, W + p.ln1g, a.m1, a.r1, pl.td, d, dx, d, G + p.ln1g, G + p.ln1b, s);
+  return t_ln_bwd(a.x, d, R, d, W + p.ln1g, a.m1, a.r1, pl.td, d, dx, d, true, G + p.ln1g, G + p.ln1b, s);
 }
 
 hipError_t stack_fwd(const float* W, const std::vector<EncP>& ps, size_t g_off, size_t b_off, Stack& st, const float* in,
@@ -367,13 +367,14 @@ hipError_t stack_fwd(const float* W, const std::vector<EncP>& ps, size_t g_off, 
 hipError_t stack_bwd(const float* W, float* G, const std::vector<EncP>& ps, size_t g_off, size_t b_off, const Stack& st,
                      const float* dout, float* dx, const Dims& D, Plan& pl, hipStream_t s) {
   const long long R = (long long)st.nseq * st.S;
-  TRY(t_fill(dx, R * D.d, 0.f, s));
   const float* xl = st.layer[D.n - 1].y;
-  if (st.first_row_only)
+  if (st.first_row_only) {
+    TRY(t_fill(dx, R * D.d, 0.f, s));
     TRY(t_ln_bwd(xl, (long long)st.S * D.d, st.nseq, D.d, W + g_off, st.mf, st.rf, dout, D.d, dx, (long long)st.S * D.d,
-                 G + g_off, G + b_off, s));
-  else
-    TRY(t_ln_bwd(xl, D.d, (int)R, D.d, W + g_off, st.mf, st.rf, dout, D.d, dx, D.d, G + g_off, G + b_off, s));
+                 false, G + g_off, G + b_off, s));
+  } else {
+    TRY(t_ln_bwd(xl, D.d, (int)R, D.d, W + g_off, st.mf, st.rf, dout, D.d, dx, D.d, false, G + g_off, G + b_off, s));
+  }
   for (int l = D.n - 1; l >= 0; --l) TRY(enc_bwd(W, G, ps[l], st.layer[l], D, st.nseq, st.S, st.valid, dx, pl, s));
   return hipSuccess;
 }
@@ -419,7 +420,7 @@ hipError_t item_bwd(const float* W, float* G, const ItemP& p, const KvP& kv, con
   TRY(linear_dx(dx, d, R, d, W + p.w2, F, pl.tF, F, false, a.a1, s));
   TRY(linear_dw(a.h3, d, R, d, pl.tF, F, F, G + p.w1, G + p.b1, s));
   TRY(linear_dx(pl.tF, F, R, F, W + p.w1, d, pl.td, d, false, nullptr, s));
-  TRY(t_ln_bwd(a.x3, d, R, d, W + p.ln3g, a.m3, a.r3, pl.td, d, dx, d, G + p.ln3g, G + p.ln3b, s));
+  TRY(t_ln_bwd(a.x3, d, R, d, W + p.ln3g, a.m3, a.r3, pl.td, d, dx, d, true, G + p.ln3g, G + p.ln3b, s));
   // cross-attention to the context
   TRY(linear_dw(a.oc, d, R, d, dx, d, d, G + p.wo2, G + p.bo2, s));
   TRY(linear_dx(dx, d, R, d, W + p.wo2, d, pl.td, d, false, nullptr, s));
@@ -429,7 +430,7 @@ hipError_t item_bwd(const float* W, float* G, const ItemP& p, const KvP& kv, con
   TRY(t_attn_bwd(ca, s));
   TRY(linear_dw(a.h2, d, R, d, pl.tq, d, d, G + p.wq, G + p.bq, s));
   TRY(linear_dx(pl.tq, d, R, d, W + p.wq, d, pl.td, d, false, nullptr, s));
-  TRY(t_ln_bwd(a.x2, d, R, d, W + p.ln2g, a.m2, a.r2, pl.td, d, dx, d, G + p.ln2g, G + p.ln2b, s));
+  TRY(t_ln_bwd(a.x2, d, R, d, W + p.ln2g, a.m2, a.r2, pl.td, d, dx, d, true, G + p.ln2g, G + p.ln2b, s));
   TRY(linear_dw(Qc, d, Rc, d, pl.dKl, d, d, G + kv.wk, G + kv.bk, s));
   TRY(linear_dw(Qc, d, Rc, d, pl.dVl, d, d, G + kv.wv, G + kv.bv, s));
   TRY(linear_dx(pl.dKl, d, Rc, d, W + kv.wk, d, pl.dQc, d, true, nullptr, s));
@@ -440,7 +441,7 @@ hipError_t item_bwd(const float* W, float* G, const ItemP& p, const KvP& kv, con
   TRY(t_attn_bwd(self_attn_bwd(self_attn(a.qkv, D, D.B, D.U, n_uniq, a.st, a.o), D, pl.td, pl.dqkv), s));
   TRY(linear_dw(a.h1, d, R, d, pl.dqkv, 3 * d, 3 * d, G + p.wqkv, G + p.bqkv, s));
   TRY(linear_dx(pl.dqkv, 3 * d, R, 3 * d, W + p.wqkv, d, pl.td, d, false, nullptr, s));
-  return t_ln_bwd(a.x, d, R, d, W + p.ln1g, a.m1, a.r1, pl.td, d, dx, d, G + p.ln1g, G + p.ln1b, s);
+  return t_ln_bwd(a.x, d, R, d, W + p.ln1g, a.m1, a.r1, pl.td, d, dx, d, true, G + p.ln1g, G + p.ln1b, s);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -508,9 +509,8 @@ hipError_t run_step(const float* W, float* G, const PMap& pm, Plan& pl, const In
   TRY(stack_bwd(W, G, pm.seq, pm.seq_g, pm.seq_b, pl.seqs, pl.dx_cross, pl.dx_seq, D, pl, s));
   TRY(t_fill(pl.dH, (long long)Ri * d, 0.f, s));
   TRY(t_assemble_bwd(pl.dx_seq, D.B, D.U, pl.slot, D.K, D.L, d, pl.dH, G + pm.cls, G + pm.pos, s));
-  TRY(t_fill(pl.dx_item, (long long)Ri * d, 0.f, s));
   TRY(t_ln_bwd(pl.item[D.n - 1].y, d, Ri, d, W + pm.item_g, pl.item_mf, pl.item_rf, pl.dH, d, pl.dx_item, d,
-               G + pm.item_g, G + pm.item_b, s));
+               false, G + pm.item_g, G + pm.item_b, s));
   TRY(t_fill(pl.dQc, (long long)D.B * D.T * d, 0.f, s));
   for (int l = D.n - 1; l >= 0; --l)
     TRY(item_bwd(W, G, pm.item[l], pm.kv[l], pl.item[l], Qc, D, pl.n_uniq, pl.dx_item, pl, s));

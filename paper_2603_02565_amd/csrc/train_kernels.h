@@ -39,10 +39,10 @@ hipError_t t_gemm(const TGemm& g, hipStream_t s);
 // Y = LN(X) * g + b per row of d values (eps 1e-5); mean and 1/std per row saved
 hipError_t t_ln_fwd(const float* X, long long x_rs, int rows, int d, const float* g, const float* b, float* Y,
                     long long y_rs, float* mean, float* rstd, hipStream_t s);
-// dX += the LayerNorm input gradient of dY; dg, db += the parameter gradients (atomically)
+// dX = (accumulate: +=) the LayerNorm input gradient of dY; dg, db += the parameter gradients (atomically)
 hipError_t t_ln_bwd(const float* X, long long x_rs, int rows, int d, const float* g, const float* mean,
-                    const float* rstd, const float* dY, long long dy_rs, float* dX, long long dx_rs, float* dg,
-                    float* db, hipStream_t s);
+                    const float* rstd, const float* dY, long long dy_rs, float* dX, long long dx_rs, bool accumulate,
+                    float* dg, float* db, hipStream_t s);
 // Multi-head attention over nseq sequences: query rows of sequence z start at q + z*q_bs (row stride
 // q_rs, head h in columns h*dh..), likewise keys, values, o and dO; Sq queries and Sk keys per
 // sequence, of which the first qlen[z] and klen[z] count (null: all; queries past them give zero
