@@ -91,3 +91,14 @@ def test_attention_reference_moves(d, H, B, T):
 ])
 def test_fp32_products(d, H, B, T, M, K, L, ffn):
     check_pass(gen.config(1, B=B, T=T, M=M, K=K, L=L, d=d, n_heads=H, ffn=ffn, n_layers=2, dtype="f32"))
+
+
+@pytest.mark.parametrize("d,H,B,T,M,K,L,dtype", [
+    (128, 4, 1, 1, 5, 1, 2, "bf16"),        # one row of a 32-row block
+    (128, 2, 2, 33, 40, 31, 3, "bf16"),     # head width 64; one row above a block, one below
+    (256, 8, 32, 601, 90, 33, 5, "bf16"),   # several blocks per wave, the last one of 25 rows
+    (64, 1, 2, 65, 64, 32, 4, "f32"),       # fp32 rows of 64, padded item rows, an exact block
+    (32, 1, 3, 31, 20, 7, 3, "f32"),
+])
+def test_linear_attention_blocks(d, H, B, T, M, K, L, dtype):
+    check_pass(gen.config(1, B=B, T=T, M=M, K=K, L=L, d=d, n_heads=H, ffn=4 * d, n_layers=1, dtype=dtype, attention="linear"))
