@@ -36,8 +36,8 @@ typedef enum { FE_LOSS_MSE = 0, FE_LOSS_BCE = 1, FE_LOSS_CE = 2 } fe_loss;
 /*
  * Workspace bytes fe_train_grads needs for B requests with T context rows, pools of M elements
  * (M = vocab for token-id items) and K lists of length L.  The workspace holds every saved
- * activation of the forward (all layers of the four modules, the attention probabilities
- * included) and the backward's scratch, so it grows with B * (T^2 + U^2 + U T + K L^2 + K^2),
+ * activation of the forward (all layers of the four modules; of an attention its output and two
+ * statistics per query and head) and the backward's scratch, so it grows with B * (T + U + K L),
  * U = min(M, K L).
  *
  * Errors: FE_EINVAL (NULL pointer, sizes < 1, L > max_L), FE_EUNSUPPORTED (a config outside the
