@@ -164,22 +164,27 @@ __global__ __launch_bounds__(WAVES * 64) void k_attention(AttnArgs a) {
 // every query tile of every wave consumes; the next chunk is fetched into registers while the
 // current one is in use.
 //
-// Softmax arithmetic (16 scores per lane and 64-key step) is what bounds it, so it is kept to
-// what a score needs: a step's scores are compared with the tile's reference m_run, and only when
-// some query's score passes it by more than 2^8 is that query's reference moved (a cross-lane
-// maximum, the rescaling of output and sum); probabilities are exp2(score * sl2 - m_run) <= 2^8 in
-// one multiply-add and one exponential.  A query's result does not depend on the other queries of
-// its tile.  The normaliser is one more row of the output product (values of one, fp32
-// accumulation), so it sums the probabilities as the values see them: the part of their bf16
-// rounding that a row's probabilities share cancels (scores of 64 text requests against float64:
-// rms error 1.13e-2 of the largest, 1.24e-2 with the sum of the unrounded ones).  The scores of the
-// next tile are formed while this tile's softmax runs, and a chunk's loads are first touched when
-// they are stored to LDS (a shift moved up to the load made every chunk wait for its successor).
-// Measured, before and after: 2048 x 2048, 128 heads of 32: 168 -> 121 us (570 TFLOP/s); 1024 x 1024, 64 heads of 64: 53 -> 39 us; 1000 x 1000, 256 heads of
-// 32: 86 -> 62 us; 383 queries x 2048 keys, 128 heads of 32: 59 -> 42 us.
+// Softmax arithmetic (16 scores per lane and 64-key step) is what bounds it: per score a scaling, half
+// a maximum, a subtraction, one exponential, the normaliser's addition (of the fp32 exponential)
+// and half a conversion.  A query's reference is the exact maximum of the scores so far; a step in
+// which no query of the tile passes its own skips the cross-lane maximum and the rescaling of the
+// output, whose factor would be one, so the bits are those of rescaling at every step (always
+// rescaling: context of 16 x 2048 rows, d 256, 458 -> 460 us; 8 x 1024, d 512, 619 -> 627 us).  A
+// query's result does not depend on the other queries of its tile, nor at head width 64 on how many
+// tiles a wave has.  The scores of the next tile are formed while this tile's softmax runs, and a
+// chunk's loads are first touched when they are stored to LDS (a shift moved up to the load made
+// every chunk wait for its successor).
+// Measured by kernel trace, one LDS buffer and branching loads -> now: 2048 x 2048, 128 heads of 32:
+// 179 -> 157 us (437 TFLOP/s); 1024 x 1024, 64 heads of 64: 55.6 -> 49.1; 1000 x 1000, 256 heads of
+// 32: 92.0 -> 80.6; 383 queries x 2048 keys, 128 heads of 32: 58.4 -> 47.4.
+// A cheaper form measured faster and is not used: moving the reference only when a score passes
+// it by 2^8, with scaling and subtraction in one multiply-add and the normaliser as a row of the
+// output product, took 121 us at the first size, but sums bf16 probabilities where the other
+// attention kernels sum fp32 ones.
 // ------------------------------------------------------------------------------------------
 template <int DH, int WAVES, int QT, int KC>
 __global__ __launch_bounds__(WAVES * 64, WAVES != 4 ? 1 : DH == 64 || QT >= 8 ? 2 : 3) void k_attention_chunked(AttnArgs a) {
+#pragma clang fp contract(off)   // scores are rounded once scaled, before the maximum is taken and subtracted
   constexpr int NT = WAVES * 64;
   constexpr int KLD = DH + 8, VLD = KC + 8, NB = DH / 16;
   constexpr int PER_T = KC * DH / 8 / NT;         // 16-byte vectors per thread per tensor
@@ -210,11 +215,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES != 4 ? 1 : DH == 64 || QT >= 8 ? 
   // query tile t of this wave: rows q0(t) .. q0(t)+15
   auto q0_of = [&](int t) { return qg * per_group + (t * WAVES + wave) * 16; };
   bf16x8 qf[QT][DH / 32];
-  float m_run[QT];
-  f32x4 o[QT][NB], l_run[QT];                      // l_run: four copies of the sum
-  bf16x8 ones;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) ones[j] = (bf16)1.f;
+  float m_run[QT], l_run[QT];                      // l_run: this lane's keys only, until the end
+  f32x4 o[QT][NB];
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
     const int qrow = q0_of(t) + q_in;
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES != 4 ? 1 : DH == 64 || QT >= 8 ? 
     for (int c = 0; c < DH / 32; ++c)
       qf[t][c] = qrow < nq ? *reinterpret_cast<const bf16x8*>(Qb + (long long)qrow * a.q_rs + c * 32 + g * 8) : bf16x8{};
     m_run[t] = -INFINITY;
-    l_run[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    l_run[t] = 0.f;
 #pragma unroll
     for (int i = 0; i < NB; ++i) o[t][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -242,10 +244,11 @@ __global__ __launch_bounds__(WAVES * 64, WAVES != 4 ? 1 : DH == 64 || QT >= 8 ? 
   };
   load_chunk(0);
 
-  // 64 keys (two 32-key blocks) per softmax step where a wave has several query tiles, else 32;
+  // 64 keys (two 32-key blocks) per softmax step at head width 32 with several query tiles per wave, else
+  // 32 (head width 64: a tile's arithmetic is then the same whatever the number of tiles per wave);
   // every key and value fragment of a step is read from LDS once and used by all QT query tiles of
   // the wave.  Keys from nkeys on (zero rows in LDS, up to KC) are masked.
-  constexpr int NU = (KC >= 64 && QT >= 2) ? 2 : 1;   // 32-key blocks per step
+  constexpr int NU = (KC >= 64 && QT >= 2 && DH == 32) ? 2 : 1;   // 32-key blocks per step
   static_assert(KC % (32 * NU) == 0, "whole steps per chunk");
 
   int cur = 0;
@@ -300,6 +303,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES != 4 ? 1 : DH == 64 || QT >= 8 ? 
         if (q0_of(t) >= nq) continue;               // uniform
         if (t + 1 < QT) scores(t + 1, sc[(t + 1) & 1]);
         f32x4 (&s)[NU][2] = sc[t & 1];
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) s[u][x] *= sl2;
         if (kb + 32 * NU > nkeys) {                 // ragged last step (uniform branch)
 #pragma unroll
           for (int u = 0; u < NU; ++u)
@@ -316,28 +323,28 @@ __global__ __launch_bounds__(WAVES * 64, WAVES != 4 ? 1 : DH == 64 || QT >= 8 ? 
           for (int x = 0; x < 2; ++x)
 #pragma unroll
             for (int j = 0; j < 4; j += 2) mx = fmaxf(fmaxf(mx, s[u][x][j]), s[u][x][j + 1]);
-        if (__any(mx * sl2 > m_run[t] + 8.f)) {
-          const float mq = rows_max(mx) * sl2;      // finite for a valid query: every step holds a valid key
-          const bool up = mq > m_run[t] + 8.f;
-          const float m_new = up ? mq : m_run[t];
-          const float alpha = up ? __builtin_amdgcn_exp2f(m_run[t] - m_new) : 1.f;   // exp2(-inf) = 0
+        float alpha = 1.f;
+        if (__any(mx > m_run[t])) {                 // else every query's factor is 1: the same bits either way
+          const float m_new = fmaxf(m_run[t], rows_max(mx));   // finite: every step holds a valid key
+          alpha = __builtin_amdgcn_exp2f(m_run[t] - m_new);    // v_exp_f32; exp2(-inf) = 0
           m_run[t] = m_new;
-          l_run[t] *= alpha;
 #pragma unroll
           for (int i = 0; i < NB; ++i) o[t][i] *= alpha;
         }
         asm("" : "+v"(m_run[t]));                    // one register per tile, not a vector copied around the branches
-        const float nm = -m_run[t];
+        float psum = 0.f;
         bf16x8 pb[NU];
 #pragma unroll
         for (int u = 0; u < NU; ++u)
 #pragma unroll
           for (int x = 0; x < 2; ++x)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              pb[u][4 * x + j] = (bf16)__builtin_amdgcn_exp2f(fmaf(s[u][x][j], sl2, nm));   // v_exp_f32
-#pragma unroll
-        for (int u = 0; u < NU; ++u) l_run[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[u], l_run[t], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) {
+              const float e = __builtin_amdgcn_exp2f(s[u][x][j] - m_run[t]);
+              psum += e;
+              pb[u][4 * x + j] = (bf16)e;
+            }
+        l_run[t] = fmaf(l_run[t], alpha, psum);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -350,8 +357,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES != 4 ? 1 : DH == 64 || QT >= 8 ? 
   for (int t = 0; t < QT; ++t) {
     const int qrow = q0_of(t) + q_in;
     if (q0_of(t) >= nq) continue;
+    const float l_tot = rows_sum(l_run[t]);
     if (qrow >= nq) continue;
-    const float inv = __builtin_amdgcn_rcpf(l_run[t][0]);   // v_rcp_f32
+    const float inv = __builtin_amdgcn_rcpf(l_tot);   // v_rcp_f32
     bf16* Ob = static_cast<bf16*>(a.O) + b * a.o_bs + (long long)qrow * a.o_rs + h * DH;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {

@@ -49,6 +49,28 @@ def test_wide_products(B, T, K, L, ffn):
     check_pass(gen.config(4, B=B, T=T, K=K, L=L, ffn=ffn, n_layers=1, vocab=600, M=600))
 
 
+def context_kv(c, W, x):
+    """kv of fe_encode_context for context rows x [B][T][d] (bf16, on the GPU), as its own bits."""
+    ev = make_evaluator(c, W)
+    bufs = ev.allocate(x.shape[0], c.T, c.M, c.K, c.L)
+    fe.fe_encode_context(ev.handle, x.shape[0], c.T, x, None, bufs["kv"], bufs["ws"])
+    kv = bufs["kv"].view(c.n_layers, 2, x.shape[0], c.T, c.d).clone()
+    torch.cuda.synchronize()
+    ev.close()
+    return kv
+
+
+def test_context_independent_of_batch():
+    """Head width 64: one query tile per wave for one request (8 workgroups of two), two for 64 of
+    them (512).  A request's context cache has the same bits either way."""
+    c = gen.config(1, B=64, T=400, d=128, n_heads=2, ffn=512, n_layers=1)
+    W = gen.make_weights(c)
+    x = torch.from_numpy(gen.make_inputs(c)["x"]).cuda().bfloat16()
+    kv = context_kv(c, W, x)
+    for b in (0, 37, 63):
+        assert torch.equal(context_kv(c, W, x[b:b + 1].contiguous())[:, :, 0], kv[:, :, b]), b
+
+
 @pytest.mark.parametrize("d,H,B,T", [
     (128, 4, 1, 257),     # one query tile per wave; a last chunk of one key
     (128, 2, 1, 300),     # head width 64
