@@ -198,91 +198,109 @@ __global__ __launch_bounds__(64 * NW, 4) void k_gemm_tiled(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Products of few rows (the cross-sequence set of a text batch: B K = 128 rows): one 32 x 32 block
-// per workgroup, its four waves each summing a quarter of K.
+// Products of few rows (the cross-sequence set of a text batch: B K = 128 rows): one wave per 32 x 32
+// block, K in the order of the tiles above, so that a row's result is the same however many rows
+// share the launch.
 //
 // Bound by latency: at 128 rows a product has a few dozen tiles, and a tiled loop of K / 64 stages
-// waits for memory once a stage.  Here both operands go straight to registers, four 16-deep steps
-// requested ahead of the four being multiplied, with no barrier until the four partial sums meet
-// in LDS; wave w then finishes columns 8w .. 8w + 7 of the block, adding the parts in wave order.
-// R = 128, before (64 x 64 tiles through LDS) -> now: K 512 N 512 6.0 -> 4.3 us, K 512 N 2048 6.1 ->
-// 4.2, K 2048 N 512 12.9 -> 7.2.  Eight waves and 32 x 64 blocks measured the same or slower.
+// waits for memory once a stage.  Here both operands go straight to registers, four batches of eight
+// 16-deep steps in flight, after the bias and residual that the epilogue adds.
+// R = 128, 64 x 64 tiles through LDS -> this kernel: K 512 N 512 5.9 -> 3.4 us, K 512 N 2048 6.0 ->
+// 3.4, K 2048 N 512 12.9 -> 6.6.  Four waves per block, each over a quarter of K with the parts added
+// in LDS, took 3.5, 3.7 and 6.7 us, and their sums differ from the tiles'.
 // ------------------------------------------------------------------------------------------
 template <int EPI>
-__global__ __launch_bounds__(64 * NW) void k_gemm_thin(GemmArgs a) {
-  constexpr int NB = 4;                                  // 16-deep steps per batch of loads
-  __shared__ __attribute__((aligned(16))) f32x4 part[NW][4][64];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__global__ __launch_bounds__(64) void k_gemm_thin(GemmArgs a) {
+  constexpr int NB = 8, NBUF = 4;                        // 16-deep steps per batch of loads; batches in flight
+  const int lane = threadIdx.x;
   const int n_nt = a.N / 32, id = xcd_tile(blockIdx.x, gridDim.x);
   const int row0 = (id / n_nt) * 32, nt = id % n_nt, row = row0 + (lane & 31);
   bool ok = row < a.R;
   if (ok && a.nvalid) ok = (row % a.rows_per_batch) < a.nvalid[row / a.rows_per_batch];
-  if (!__any(ok)) return;                                // the same in every wave
+  if (!__any(ok)) return;
   if (a.zero && blockIdx.x == 0)
-    for (int i = threadIdx.x; i < a.zero_n; i += 64 * NW) a.zero[i] = 0;
-  const int KS = a.K / 16, per = KS / NW, k0 = wave * per, nb = per / NB;
-  const bf16* Al = static_cast<const bf16*>(a.A) + (long long)(ok ? row : row0) * a.lda + 8 * (lane >> 5) + k0 * 16;
-  const bf16x8* Wl = static_cast<const bf16x8*>(a.Wt) + ((long long)nt * KS + k0) * 64 + lane;
+    for (int i = lane; i < a.zero_n; i += 64) a.zero[i] = 0;
+  const int nb = a.K / (16 * NB);                        // at least 1: K is a multiple of 128
+  // Batches past the last get offsets past the buffers (zeros, no traffic), so that no branch separates
+  // the loads and every wait counts only the batch it needs.
+  const auto ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(static_cast<const bf16*>(a.A)) + (long long)row0 * a.lda, 0,
+                                                    32 * a.lda * 2, 0x00027000);
+  const auto rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(static_cast<const bf16*>(a.Wt)) + (long long)nt * a.K * 32, 0,
+                                                    a.K * 32 * 2, 0x00027000);
+  constexpr unsigned OUT = 0x80000000u;
+  const unsigned a0 = ((ok ? row - row0 : 0) * a.lda + 8 * (lane >> 5)) * 2u, w0 = lane * 16u;
+  // what the epilogue adds (the lane holds columns n0 + 8q + 0..3 of its row), requested first of all
+  const int n0 = nt * 32 + 4 * (lane >> 5);
+  f32x4 bias[4], res[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    bias[q] = a.bias ? *reinterpret_cast<const f32x4*>(a.bias + n0 + 8 * q) : f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (EPI == EPI_RESID) {
+      const long long at = (long long)(ok ? row : row0) * a.ldr + n0 + 8 * q;
+      if (a.res_f32) {
+        res[q] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.res) + at);
+      } else {
+        const bf16x4 t = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(a.res) + at);
+        res[q] = f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
+      }
+    }
+  }
   f32x16 acc = f32x16{};
-  bf16x8 af[2][NB], wf[2][NB];
+  u32x4 af[NBUF][NB], wf[NBUF][NB];
   auto load = [&](int t, int b) {
+    const unsigned ao = t < nb ? a0 + t * (NB * 32u) : OUT, wo = t < nb ? w0 + t * (NB * 1024u) : OUT;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      af[b][i] = *reinterpret_cast<const bf16x8*>(Al + (t * NB + i) * 16);
-      wf[b][i] = Wl[(t * NB + i) * 64];
+      af[b][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, ao + i * 32u, 0, 0);
+      wf[b][i] = __builtin_amdgcn_raw_buffer_load_b128(rw, wo + i * 1024u, 0, 0);
     }
   };
-  auto mul = [&](int b) {
 #pragma unroll
-    for (int i = 0; i < NB; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][i], af[b][i], acc, 0, 0, 0);
-  };
-  load(0, 0);
-  for (int t = 0; t < nb; t += 2) {
-    if (t + 1 < nb) load(t + 1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    mul(0);
-    if (t + 1 >= nb) break;
-    if (t + 2 < nb) load(t + 2, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    mul(1);
+  for (int b = 0; b < NBUF; ++b) {
+    load(b, b);
+    __builtin_amdgcn_sched_barrier(0);                   // in this order: the waits below count on it
   }
+  for (int t = 0; t < nb; t += NBUF) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) part[wave][q][lane] = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-  __syncthreads();
-  if (!ok) return;
-  f32x4 o = part[0][wave][lane];
+    for (int b = 0; b < NBUF; ++b) {
 #pragma unroll
-  for (int w = 1; w < NW; ++w) o += part[w][wave][lane];
-  const int n = nt * 32 + 8 * wave + 4 * (lane >> 5);
-  const float4 bb = a.bias ? *reinterpret_cast<const float4*>(a.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-  o += f32x4{bb.x, bb.y, bb.z, bb.w};
-  if constexpr (EPI == EPI_RESID) {
-    float4 rv;
-    if (a.res_f32) {
-      rv = *reinterpret_cast<const float4*>(static_cast<const float*>(a.res) + (long long)row * a.ldr + n);
-    } else {
-      const bf16x4 t = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(a.res) + (long long)row * a.ldr + n);
-      rv = make_float4((float)t[0], (float)t[1], (float)t[2], (float)t[3]);
+      for (int i = 0; i < NB; ++i)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[b][i]), __builtin_bit_cast(bf16x8, af[b][i]), acc,
+                                                        0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      load(t + b + NBUF, b);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    *reinterpret_cast<float4*>(static_cast<float*>(a.C) + (long long)row * a.ldc + n) =
-        make_float4(rv.x + o[0], rv.y + o[1], rv.z + o[2], rv.w + o[3]);
-  } else {
-    bf16x4 h;
+  }
+  if (!ok) return;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) h[e] = (bf16)(EPI == EPI_RELU ? fmaxf(o[e], 0.f) : o[e]);
-    *reinterpret_cast<bf16x4*>(static_cast<bf16*>(a.C) + (long long)(n / a.col_block) * a.col_block_stride + (long long)row * a.ldc +
-                               n % a.col_block) = h;
+  for (int q = 0; q < 4; ++q) {
+    const int n = n0 + 8 * q;
+    const f32x4 o = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]} + bias[q];
+    if constexpr (EPI == EPI_RESID) {
+      *reinterpret_cast<f32x4*>(static_cast<float*>(a.C) + (long long)row * a.ldc + n) = res[q] + o;
+    } else {
+      bf16x4 h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = (bf16)(EPI == EPI_RELU ? fmaxf(o[e], 0.f) : o[e]);
+      *reinterpret_cast<bf16x4*>(static_cast<bf16*>(a.C) + (long long)(n / a.col_block) * a.col_block_stride + (long long)row * a.ldc +
+                                 n % a.col_block) = h;
+    }
   }
 }
 
 template <int EPI>
 hipError_t launch_epi(const GemmArgs& a, hipStream_t s) {
-  // Few blocks take the split-K form: it needs K / 16 steps to divide over four waves in batches of
-  // four.  Up to 512 blocks it was faster at every K measured (R = 512: K 2048 N 512 7.5 against
-  // 13 us); from 768 blocks on, at K = 512, the tiles are level or ahead (R = 512 N 1536: 6.6 us both).
+  // Up to 256 blocks (one wave per compute unit) the thin form is ahead at every K and N measured (K 384
+  // to 4096, N 384 to 4096: 3.4 to 11.3 us, tiles 5.1 to 24 us).  With more, two waves of a compute
+  // unit share its L1 and it takes half as long again: at 257 to 512 blocks it is ahead in the
+  // residual products (N = 512, few tiles; K 512 R 768: 5.3 against 6.4 us, K 2048: 11.7 against
+  // 13.2) and level in the others (K 512, N 2048, R 256: 5.1 against 5.2).  Beyond, the tiles are ahead (K
+  // 512, N 1536, R 384: 5.2 against 6.7; K 2048, N 512, R 2048: 13.7 against 22).  Tiles of 64 x 64 were 5%
+  // ahead of these at K 384 to 640, N 512, R 2048 (6.4 against 6.7 us at K 512) and behind elsewhere.
   const long long blocks = (long long)((a.R + 31) / 32) * (a.N / 32);
-  if (blocks <= 512 && a.K % 256 == 0)
-    hipLaunchKernelGGL((k_gemm_thin<EPI>), dim3((unsigned)blocks), dim3(64 * NW), 0, s, a);
+  if (blocks <= 512)
+    hipLaunchKernelGGL((k_gemm_thin<EPI>), dim3((unsigned)blocks), dim3(64), 0, s, a);
   else
     hipLaunchKernelGGL((k_gemm_tiled<EPI>), dim3((unsigned)(((a.R + BM - 1) / BM) * (a.N / BN))), dim3(64 * NW), 0, s, a);
   return hipGetLastError();

@@ -49,6 +49,20 @@ def test_wide_products(B, T, K, L, ffn):
     check_pass(gen.config(4, B=B, T=T, K=K, L=L, ffn=ffn, n_layers=1, vocab=600, M=600))
 
 
+def test_wide_request_independent_of_batch():
+    """Wide models: few rows take one product kernel, many the other (one request's 144 item and 16 list
+    rows against those of 24 requests), and head width 64 one or two query tiles per wave.  A request's
+    results have the same bits whoever shares the batch."""
+    c = gen.config(4, B=24, T=300, K=16, L=9, n_layers=1, vocab=600, M=600)
+    W, I = gen.make_weights(c), gen.make_inputs(c)
+    whole = run_pass(c, W, I)
+    for b in (0, 23):
+        one = run_pass(c, W, {k: None if v is None else v[b:b + 1] for k, v in I.items()})
+        assert np.array_equal(one["kv"][:, :, 0], whole["kv"][:, :, b]), ("kv", b)
+        for k in ("H", "seq", "Cp", "scores"):
+            assert np.array_equal(one[k][0], whole[k][b]), (k, b)
+
+
 def context_kv(c, W, x):
     """kv of fe_encode_context for context rows x [B][T][d] (bf16, on the GPU), as its own bits."""
     ev = make_evaluator(c, W)
