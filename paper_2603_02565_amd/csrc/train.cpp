@@ -279,11 +279,15 @@ hipError_t linear_dw(const float* X, long long x_rs, int R, int din, const float
   g.beta = 1.f;
   // (row chunk x output tile) workgroups: two per compute unit -- every chunk adds its whole tile
   // atomically, and with four per compute unit those sums cost more than the waves hide (the
-  // recommendation batch's gradients 1052 us; 913 at 512 workgroups, 964 at 256) -- in chunks of at least
-  // 64 rows (two k steps)
+  // recommendation batch's gradients 1052 us; 913 at 512 workgroups, 964 at 256; whole steps of nine
+  // other shapes, d 64 to 256, 800 to 35000 rows: 256 workgroups 0.98 to 1.02 times as fast, 1024 0.96
+  // to 1.01) -- in chunks of at least 64 rows (two k steps; 256 rows: a step of 385 context rows 1051
+  // -> 1225 us).  The head's one column takes chunks of at least 256 rows: its terms cancel (under the
+  // listwise loss the row weights of a request sum to zero, and its lists are alike), so what the
+  // order of the sum leaves is largest there, and short chunks save nothing (1051 us both ways).
   const long long tiles = (long long)((din + 63) / 64) * ((dout + 63) / 64);
   long long chunks = std::max(1LL, 512 / tiles);
-  long long ks = std::max(64LL, (R + chunks - 1) / chunks);
+  long long ks = std::max(dout == 1 ? 256LL : 64LL, (R + chunks - 1) / chunks);
   g.ksplit = (int)((ks + 31) / 32 * 32);
   g.colsum = db;
   return t_gemm(g, s);

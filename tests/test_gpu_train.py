@@ -240,3 +240,16 @@ def test_attention_edges(d, heads, B, T, K, L, M):
     c = gen.config(1, B=B, T=T, K=K, L=L, M=M, d=d, n_heads=heads, ffn=2 * d, n_layers=1, dtype="f32")
     W, I = gen.make_weights(c), gen.make_inputs(c)
     check(c, W, I, _relevance(c), "bce")
+
+
+def test_head_gradient_repeats():
+    """The head's weight gradient under the listwise loss sums terms that nearly cancel.  Up to 512 rows
+    (here 400 lists) its sum has one order, so every step gives the same bits."""
+    c = gen.config(4, B=4, T=10, K=100, L=5, vocab=300, M=300, n_layers=1, d=64, n_heads=2, ffn=256, dtype="f32")
+    W, I = gen.make_weights(c), gen.make_inputs(c)
+    a = _relevance(c)
+    first = run_train(c, W, I, a, "ce")
+    for _ in range(4):
+        loss, g, s = run_train(c, W, I, a, "ce")
+        assert np.array_equal(s, first[2])
+        assert np.array_equal(g["head.w"], first[1]["head.w"])
