@@ -238,7 +238,8 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int kc0, int tiles_n, int
 // Attention of the training step, forward and backward, per (sequence, head): scores and
 // probabilities stay on chip.  The forward keeps each query's maximum m and 1 / l of its normaliser
 // l = sum exp(score - m) (infinity and 0 for a query that attends to nothing), from which the
-// backward forms the forward's probabilities again.
+// backward forms the forward's probabilities again: the same products in the same order, the score
+// scaled, the maximum taken off and the exponential scaled by 1 / l with a rounding each.
 //
 // Everything is a product of TS x TS blocks on the fp32 matrix cores (TS = 32: 32x32x2, TS = 16:
 // 16x16x4; NS = 64 / TS k slots).  Accumulator a of a lane in slot g is block row
@@ -256,8 +257,9 @@ __global__ __launch_bounds__(256) void k_gemm(TGemm g, int kc0, int tiles_n, int
 // A wave owns TS queries (forward, dQ: blocks are [key][query]) or TS keys (dK and dV: blocks are
 // [query][key]) and walks the other side in tiles that the workgroup stages in LDS, the next tile's
 // loads in flight; sequences of up to TS rows (SMALL) take one wave each instead.  Bound by the fp32
-// matrix rate (2 products forward, 7 backward: S and dP are formed in both orientations, which costs
-// less than moving dS through memory or adding dQ atomically).  Measured, before (probabilities
+// matrix rate (2 products forward up to 256 keys, 4 beyond, where the scores are formed anew for the
+// maximum, the sum and the probabilities; 7 backward: S and dP are formed in both orientations, which
+// costs less than moving dS through memory or adding dQ atomically).  Measured, before (probabilities
 // through memory, a launch per product) and after: 256 x 256, 256 heads of 32: forward 69 -> 32 us,
 // backward 117 -> 79 us; 11 x 11, 12800 heads of 32: forward 62 -> 18 us, backward 118 -> 32 us; 77 x
 // 77, 10 heads of 32: forward 16 -> 12 us, backward 33 -> 15 us.
@@ -486,7 +488,6 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd(TAttn a) {
         T::cols_by(tile, s[t], o);
       }
   } else {
-    const bool fused = a.Sk > 512;                  // exp's argument with one rounding
     for (int k0 = 0; k0 < P.nk; k0 += TS) {
       const bool more = k0 + TS < P.nk;
       const float* tile = next(K, a.k_rs, more ? k0 + TS : 0);
@@ -499,10 +500,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd(TAttn a) {
     auto probs = [&](const float* tile, int k0) {
       s[0] = T::rows_by(tile, qf);
 #pragma unroll
-      for (int i = 0; i < T::NA; ++i) {
-        const float x = fused ? fmaf(s[0][i], a.scale, -m) : s[0][i] * a.scale - m;
-        s[0][i] = k0 + T::row(i) < P.nk ? expf(x) : 0.f;
-      }
+      for (int i = 0; i < T::NA; ++i) s[0][i] = k0 + T::row(i) < P.nk ? expf(s[0][i] * a.scale - m) : 0.f;
     };
     typename T::acc_t part[2] = {};
     for (int k0 = 0; k0 < P.nk; k0 += TS) {
@@ -533,6 +531,7 @@ FE_DEV void attn_kv_tile(const float* Qt, const float* Ot, const float2* stat, c
                          const float4 (&kf)[AttnTile<TS, DH>::NQ], const float4 (&vf)[AttnTile<TS, DH>::NQ],
                          typename AttnTile<TS, DH>::acc_t (&dk)[AttnTile<TS, DH>::NB],
                          typename AttnTile<TS, DH>::acc_t (&dv)[AttnTile<TS, DH>::NB]) {
+#pragma clang fp contract(off)   // the forward's probabilities
   using T = AttnTile<TS, DH>;
   typename T::acc_t p = T::rows_by(Qt, kf), ds = T::rows_by(Ot, vf);
 #pragma unroll
@@ -551,6 +550,7 @@ template <int TS, int DH>
 FE_DEV void attn_q_tile(const float* Kt, const float* Vt, float2 st, float D, float scale, int nk,
                         const float4 (&qf)[AttnTile<TS, DH>::NQ], const float4 (&of)[AttnTile<TS, DH>::NQ],
                         typename AttnTile<TS, DH>::acc_t (&dq)[AttnTile<TS, DH>::NB]) {
+#pragma clang fp contract(off)   // the forward's probabilities
   using T = AttnTile<TS, DH>;
   typename T::acc_t p = T::rows_by(Kt, qf), ds = T::rows_by(Vt, of);
 #pragma unroll

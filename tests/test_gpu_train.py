@@ -253,3 +253,18 @@ def test_head_gradient_repeats():
         loss, g, s = run_train(c, W, I, a, "ce")
         assert np.array_equal(s, first[2])
         assert np.array_equal(g["head.w"], first[1]["head.w"])
+
+
+def test_scores_independent_of_pool_size():
+    """A request's scores have the same bits whatever the capacity of its item set (elements nobody lists
+    are padding): keys in registers up to 256, formed anew beyond, and past 512."""
+    c = gen.config(1, B=1, T=16, K=70, L=10, M=190, d=64, n_heads=2, ffn=128, n_layers=1, dtype="f32")
+    W, I = gen.make_weights(c), gen.make_inputs(c)
+    W["item.0.wqkv"] = W["item.0.wqkv"] * 8       # scores of some size, so that their rounding shows
+    want = run_train(c, W, I, _relevance(c), "bce")[2]
+    for M in (256, 257, 512, 513, 600):
+        cm = gen.config(1, B=1, T=16, K=70, L=10, M=M, d=64, n_heads=2, ffn=128, n_layers=1, dtype="f32")
+        pool = gen.make_inputs(cm)["pool"].copy()
+        pool[:, :c.M] = I["pool"]
+        got = run_train(cm, W, dict(I, pool=pool), _relevance(cm), "bce")[2]
+        assert np.array_equal(got, want), M
