@@ -153,16 +153,16 @@ def test_full_recsys_batch():
 
 
 def test_long_context():
-    """The long-context model shape (d 256, 8 heads) over 2048 context rows: score rows longer than
-    512 keys take the softmax path that re-reads them from memory."""
+    """The long-context model shape (d 256, 8 heads) over 2048 context rows: far more than 256 keys, so
+    the scores of a 32-key tile are formed anew for the maximum, the sum and the probabilities."""
     c = gen.config(3, B=1, T=2048, K=4, L=5, M=30, n_layers=1, dtype="f32")
     W, I = gen.make_weights(c), gen.make_inputs(c)
     check(c, W, I, _relevance(c), "ce")
 
 
 def test_many_lists():
-    """300 lists per request: cross-sequence score rows of 300 keys (eight per lane in registers),
-    and a loss over 300 scores."""
+    """300 lists per request: cross-sequence attention over 300 keys (scores formed anew, a last tile of
+    12 keys), and a loss over 300 scores."""
     c = gen.config(1, B=1, T=16, K=300, L=3, M=150, n_layers=1, dtype="f32")
     W, I = gen.make_weights(c), gen.make_inputs(c)
     check(c, W, I, _relevance(c), "bce")
@@ -233,7 +233,7 @@ def test_product_edges(d, heads, B, T, K, L, M):
     (64, 1, 2, 17, 5, 16, 33),       # head width 64, 17 rows: 32-row tile of a wave
     (32, 1, 1, 256, 130, 2, 129),    # the last length whose scores stay in registers; one row past 128
     (64, 1, 1, 257, 3, 4, 12),       # the first length whose scores are formed anew, head width 64
-    (32, 1, 1, 545, 3, 4, 12),       # past 512 keys, 33 rows in the last workgroup
+    (32, 1, 1, 545, 3, 4, 12),       # 33 rows in the last workgroup, a last tile of one key
 ])
 def test_attention_edges(d, heads, B, T, K, L, M):
     """Edges of the attention kernels' tiles and forms, forward (scores) and backward."""
@@ -268,3 +268,17 @@ def test_scores_independent_of_pool_size():
         pool[:, :c.M] = I["pool"]
         got = run_train(cm, W, dict(I, pool=pool), _relevance(cm), "bce")[2]
         assert np.array_equal(got, want), M
+
+
+@pytest.mark.parametrize("d, heads, B, T", [
+    (512, 8, 2, 21),       # rows in two loads per lane
+    (64, 2, 17, 485),      # 8245 rows: two groups of four rows per wave, the last wave's of four and one
+    (128, 4, 17, 485),
+    (256, 8, 17, 485),
+])
+def test_layernorm_forms(d, heads, B, T):
+    """The register forms of the LayerNorm and its backward: every width, and more rows than one group
+    per wave holds."""
+    c = gen.config(1, B=B, T=T, K=3, L=2, M=9, d=d, n_heads=heads, ffn=64, n_layers=1, dtype="f32")
+    W, I = gen.make_weights(c), gen.make_inputs(c)
+    check(c, W, I, _relevance(c), "bce")
