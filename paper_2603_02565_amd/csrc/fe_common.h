@@ -91,13 +91,6 @@ FE_DEV float wave_sum(float v) {
   v += dpp<0x4e>(v);
   return v + dpp<0xb1>(v);
 }
-FE_DEV float wave_max(float v) {
-  v = rows_max(v);
-  v = fmaxf(v, dpp<0x128>(v));
-  v = fmaxf(v, dpp<0x124>(v));
-  v = fmaxf(v, dpp<0x4e>(v));
-  return fmaxf(v, dpp<0xb1>(v));
-}
 // ... over the 32 lanes of a wave half.
 FE_DEV float half_sum(float v) {
   auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);

@@ -744,9 +744,11 @@ __global__ __launch_bounds__(256) void k_ln_fwd(const float* X, long long x_rs, 
 }
 
 // The same for d = 64 V NC, LN_ROWS rows per wave: a row and the vectors stay in registers (one
-// memory round trip instead of one per pass over the row), and the rows' reductions overlap.  Same
-// sums in the same order and with the same roundings (the multiply-adds are written out).
-// Measured, before and after: 35200 x 128 12.9 -> 8.7 us, 16384 x 128 7.4 -> 5.7 us.
+// memory round trip instead of one per pass over the row), and the rows' reductions overlap.  A lane
+// sums its V adjacent columns of each chunk of 64 V (above: every 64th column) before the tree over
+// the lanes, so the order of a row's sums depends on d, and on the alignment that picks the form, but
+// not on the number of rows.  Measured, before and after: 35200 x 128 12.9 -> 8.7 us, 16384 x 128 7.4 ->
+// 5.7 us.
 constexpr int LN_ROWS = 4;
 template <int V, int NC>
 __global__ __launch_bounds__(256) void k_ln_fwd_rows(const float* X, long long x_rs, int rows, int d, const float* g,
