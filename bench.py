@@ -159,21 +159,17 @@ def naive_flops(c, U):
 def train_flops(c, U):
     """Algorithmic flops of one training step (forward + backward) over the valid rows: every
     product of the forward once, and twice more in the backward (input and weight gradients of a
-    projection; dP, dV, dQ, dK of an attention).  U: distinct elements per request."""
-    d, F, H, n, dh = c.d, c.ffn, c.n_heads, c.n_layers, c.d // c.n_heads
+    projection; dP, dV, dQ, dK of an attention).  The last SeqEnc block counts keys and values of every
+    row and the rest of the [CLS] rows only: no other row of it reaches the loss (the step computes them
+    all the same).  U: distinct elements per request."""
+    d, F, n = c.d, c.ffn, c.n_layers
     B, T, K, S = c.B, c.T, c.K, c.L + 1
-    Usum = float(sum(U))
-
-    def enc(rows, att):                      # one encoder block: projections, FFN, attention
-        return 2 * rows * (4 * d * d + 2 * d * F) + att
-    fwd = n * enc(B * T, 4 * B * H * T * T * dh)
-    fwd += n * 2 * (2 * B * T * d * d)                                  # context keys and values per item layer
-    fwd += n * (2 * Usum * (6 * d * d + 2 * d * F)
-                + 4 * H * dh * sum(u * u + u * T for u in U))          # item-set layers
-    fwd += n * enc(B * K * S, 4 * B * K * H * S * S * dh)              # SeqEnc
-    fwd += n * enc(B * K, 4 * B * H * K * K * dh)                      # cross-sequence module
-    fwd += 2 * B * K * d
-    return 3 * fwd
+    fwd = sum(module_parts(d, F, n, B * T, B, T))
+    fwd += n * 4.0 * B * T * d * d                                      # context keys and values per item layer
+    fwd += sum(n * (u * (12.0 * d * d + 4.0 * d * F) + 4.0 * d * (u * u + u * T)) for u in U)   # item-set layers
+    fwd += sum(module_parts(d, F, n, B * K * S, B * K, S, True))       # SeqEnc
+    fwd += sum(module_parts(d, F, n, B * K, B, K))                     # cross-sequence module
+    return 3.0 * (fwd + 2.0 * B * K * d)
 
 
 def cpu_baseline(c, W, I, seconds: float):

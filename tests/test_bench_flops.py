@@ -45,3 +45,12 @@ def test_fused_cross_attention_carries_the_item_projections():
     attn = sum(n * (4.0 * u * u * d + 4.0 * u * T * d) for u in U) + n * 6.0 * d * d * rows + n * 4.0 * d * d * rows
     attn += n * 4.0 * c.B * T * T * d + n * 6.0 * d * d * c.B * T           # context self-attention with its q|k|v
     assert f["attention"] == pytest.approx(attn, rel=1e-12)
+
+
+@pytest.mark.parametrize("cid,kw", [(1, {"dtype": "f32"}), (0, {})])
+def test_training_step_counts_three_forwards(cid, kw):
+    """A training step is the joint pass and the head once forward and twice backward, in the work the
+    method needs (the last sequence-encoder block's [CLS] rows)."""
+    c = gen.config(cid, **kw)
+    U = [min(c.M, c.K * c.L) - 3] * c.B
+    assert bench.train_flops(c, U) == pytest.approx(3.0 * (_joint_total(c, U) + 2.0 * c.B * c.K * c.d), rel=1e-12)
