@@ -528,8 +528,8 @@ def main() -> int:
     if args.copy_calibration:
         return copy_calibration()
     if args.gpus != 1:
-        print(f"bench.py runs on one GPU only (the joint pass shards over independent requests; "
-              f"see DESIGN.md); got --gpus {args.gpus}", file=sys.stderr)
+        print(f"bench.py runs on one GPU only (the joint pass shards over independent "
+              f"requests); got --gpus {args.gpus}", file=sys.stderr)
         return 2
 
     import numpy as np

@@ -192,9 +192,10 @@ __global__ __launch_bounds__(256) void k_lin_merge(const float* __restrict__ par
 // twice, and the denominator is that half's dot product with z plus the other half's.  Each lane
 // then holds 4 consecutive columns per accumulator group; a lane swap between the halves makes
 // that 8 (16-byte stores of bf16 rows).  The next block's rows are requested before this block's
-// products.  Bound by memory: with a thread per (row, 8 columns) every row's phi was formed DH/8
-// times and the state was read from LDS once per row.  16 x 2048 rows, 8 heads of 32: 20.1 ->
-// 12.9 us (33 MB).  Rows r >= rpb or r >= nvalid[b] are not written.
+// products.  Bound by the latency of rows and state, for which the waves wait 58% of their time: 16 x
+// 2048 rows, 8 heads of 32 take 12.9 us, 33 MB at 2.6 TB/s, half the rate of a large copy.  With a thread
+// per (row, 8 columns), every row's phi formed DH/8 times and the state read from LDS once per row, they
+// took 20.1 us.  Rows r >= rpb or r >= nvalid[b] are not written.
 // ------------------------------------------------------------------------------------------
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void k_lin_apply(const T* __restrict__ Q, int q_rs, const float* __restrict__ St,
