@@ -187,21 +187,22 @@ __global__ __launch_bounds__(256) void k_lin_merge(const float* __restrict__ par
 
 // ------------------------------------------------------------------------------------------
 // Apply: out^T = S^T phi(q)^T on the fp32 matrix cores (32x32x2).  A wave holds the state of one
-// (batch, head) in registers (lane l: S[i][32 jb + l%32] for the i of its half, DH/2 (l/32) + t at product t) and
-// walks blocks of 32 query rows; lane l forms phi of its half of row l%32, so nothing is computed
-// twice, and the denominator is that half's dot product with z plus the other half's.  Each lane
-// then holds 4 consecutive columns per accumulator group; a lane swap between the halves makes
-// that 8 (16-byte stores of bf16 rows).  The next block's rows are requested before this block's
-// products.  Bound by the latency of rows and state, for which the waves wait 58% of their time: 16 x
-// 2048 rows, 8 heads of 32 take 12.9 us, 33 MB at 2.6 TB/s, half the rate of a large copy.  With a thread
-// per (row, 8 columns), every row's phi formed DH/8 times and the state read from LDS once per row, they
-// took 20.1 us.  Rows r >= rpb or r >= nvalid[b] are not written.
+// (batch, head) in registers (lane l at product t: S[2t + l/32][32 jb + l%32]) and walks blocks of 32
+// query rows; lane l forms phi of every other value of row l%32 (those of its half's parity), so
+// nothing is computed twice.  The sums run over the features in ascending order, two a product, like the
+// denominator's multiply-adds, for which a lane swap fetches the other half's value: a row's result is
+// that of one thread summing in order.  Each lane then holds 4 consecutive columns per accumulator
+// group; a lane swap between the halves makes that 8 (16-byte stores of bf16 rows).  The next block's
+// rows are requested before this block's products.  Bound by the latency of rows and state.  16 x 2048
+// rows, 8 heads of 32 (33 MB), a thread per (row, 8 columns) with the state in LDS and every row's phi
+// formed DH/8 times -> now: 20.1 -> 15.4 us (halves of the features summed apart: 13.4).  Rows r >= rpb
+// or r >= nvalid[b] are not written.
 // ------------------------------------------------------------------------------------------
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void k_lin_apply(const T* __restrict__ Q, int q_rs, const float* __restrict__ St,
                                                    int rpb, const int32_t* __restrict__ nvalid, int H, int groups,
                                                    int bpw, T* __restrict__ O, int o_rs) {
-  constexpr int HK = DH / 2, NB = DH / 32, QV = HK * (int)sizeof(T) / 16, PV = 16 / (int)sizeof(T);
+  constexpr int HK = DH / 2, NB = DH / 32, QV = DH * (int)sizeof(T) / 16, PV = 16 / (int)sizeof(T);
   const int id = xcd_tile(blockIdx.x, gridDim.x);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // heads are neighbours: two of them share each line of the rows
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(256) void k_lin_apply(const T* __restrict__ Q, int 
   // blocks first .. last - 1 of this wave
   const int first = (g * 4 + wave) * bpw, last = min((rpb + 31) / 32, first + bpw);
   if (first >= last) return;
-  const T* Qh = Q + (long long)b * rpb * q_rs + h * DH + half * HK;
+  const T* Qh = Q + (long long)b * rpb * q_rs + h * DH;
   uint4 qv[QV];
   auto load = [&](int blk) {                       // any row below rpb: its address needs no valid count
     const uint4* src = reinterpret_cast<const uint4*>(Qh + (long long)min(blk * 32 + c, rpb - 1) * q_rs);
@@ -220,33 +221,41 @@ __global__ __launch_bounds__(256) void k_lin_apply(const T* __restrict__ Q, int 
   load(first);
   const int n = nvalid ? min(rpb, nvalid[b]) : rpb;
   const float* src = St + (long long)bh * (DH + 1) * DH;
-  float S[NB][HK], z[HK];
+  float S[NB][HK], z[DH];                          // z: the same in every lane
+#pragma unroll
+  for (int i = 0; i < DH; ++i) z[i] = src[DH * DH + i];
 #pragma unroll
   for (int t = 0; t < HK; ++t) {
-    z[t] = src[DH * DH + half * HK + t];
 #pragma unroll
-    for (int jb = 0; jb < NB; ++jb) S[jb][t] = src[(half * HK + t) * DH + jb * 32 + c];
+    for (int jb = 0; jb < NB; ++jb) S[jb][t] = src[(2 * t + half) * DH + jb * 32 + c];
   }
   for (int blk = first; blk < last && blk * 32 < n; ++blk) {
-    float f[HK], den = 0.f;
+    float f[HK];
 #pragma unroll
     for (int i = 0; i < QV; ++i) {
-      const T* e = reinterpret_cast<const T*>(&qv[i]);
+      const unsigned x[4] = {qv[i].x, qv[i].y, qv[i].z, qv[i].w};
+      if constexpr (sizeof(T) == 2) {
 #pragma unroll
-      for (int k = 0; k < PV; ++k) f[i * PV + k] = phi(to_f32(e[k]));
+        for (int k = 0; k < 4; ++k) f[4 * i + k] = phi(__uint_as_float(half ? x[k] & 0xffff0000u : x[k] << 16));
+      } else {
+        f[2 * i] = phi(__uint_as_float(half ? x[1] : x[0]));
+        f[2 * i + 1] = phi(__uint_as_float(half ? x[3] : x[2]));
+      }
     }
     if (blk + 1 < last) load(blk + 1);
     f32x16 acc[NB];
+    float den = 0.f;
 #pragma unroll
     for (int jb = 0; jb < NB; ++jb) acc[jb] = f32x16{};
 #pragma unroll
     for (int t = 0; t < HK; ++t) {
-      den = fmaf(f[t], z[t], den);
+      const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(f[t]), __float_as_uint(f[t]), false, false);
+      den = fmaf(__uint_as_float(w[0]), z[2 * t], den);
+      den = fmaf(__uint_as_float(w[1]), z[2 * t + 1], den);
 #pragma unroll
       for (int jb = 0; jb < NB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(S[jb][t], f[t], acc[jb], 0, 0, 0);
     }
-    const auto dd = __builtin_amdgcn_permlane32_swap(__float_as_uint(den), __float_as_uint(den), false, false);
-    const float inv = 1.f / (__uint_as_float(dd[0]) + __uint_as_float(dd[1]));
+    const float inv = 1.f / den;
     const int r = blk * 32 + c;
     T* orow = O + ((long long)b * rpb + r) * o_rs + h * DH;
 #pragma unroll

@@ -141,3 +141,38 @@ def test_linear_naive_evaluator_matches_joint_pass():
         check_scores(c, naive["scores"][b].cpu().numpy(), int(naive["best"][b]), ref[b]["scores"], ("naive", b))
         check_scores(c, joint["scores"][b].cpu().numpy(), int(joint["best"][b]), ref[b]["scores"], ("joint", b))
     ev.close()
+
+
+@pytest.mark.parametrize("dh", [32, 64])
+def test_apply_sums_features_in_order(dh):
+    """The state applied to a query is a sum over the features in ascending order, in fp32 multiply-adds
+    (so every row's result is that of one thread, whatever the tiling).  Features of non-negative queries
+    are q + 1 in one rounding, so numpy gives the same bits; its multiply-adds go through float64, whose
+    second rounding can turn one in 2^29."""
+    import ctypes
+
+    import torch
+    apply = fe.load_library()._Z16launch_lin_applyPKviPKfiiPKiiiPvibP12ihipStream_t
+    apply.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_int,
+                      ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_bool, ctypes.c_void_p]
+    B, rows, H = 3, 45, 2
+    r = np.random.default_rng(dh)
+    q = r.random((B, rows, H, dh), np.float32)
+    st = r.standard_normal((B, H, dh + 1, dh)).astype(np.float32)
+    st[:, :, dh] = r.random((B, H, dh), np.float32) + 1
+    qt, stt = torch.from_numpy(q).cuda(), torch.from_numpy(st).cuda()
+    out = torch.full_like(qt, float("nan"))
+    assert apply(qt.data_ptr(), H * dh, stt.data_ptr(), B, rows, None, H, dh, out.data_ptr(), H * dh, False,
+                 torch.cuda.current_stream().cuda_stream) == 0
+    f = q + np.float32(1)
+    fma = lambda a, b, c: (a.astype(np.float64) * b + c).astype(np.float32)
+    acc, den = np.zeros(q.shape, np.float32), np.zeros(q.shape[:3] + (1,), np.float32)
+    for i in range(dh):
+        fi = f[..., i:i + 1]
+        acc = fma(fi, st[:, None, :, i, :], acc)
+        den = fma(fi, st[:, None, :, dh, i:i + 1], den)
+    want = acc * (np.float32(1) / den)
+    got = out.cpu().numpy()
+    assert np.mean(got != want) <= 1e-3
+    assert np.max(np.abs(got - want)) <= 1e-6 * np.max(np.abs(want))
+
